@@ -31,8 +31,8 @@ CSRC = os.path.join(ROOT, "paper_2411_15997_amd", "csrc")
 STAGE_SRC = {
     "cost": ["fs_cost.hip"],
     "throttle": ["fs_throttle.hip"],
-    # the dominant kernel of the stage, k_schedule_onchip, and the header it shares
-    "schedule": ["fs_sched_onchip.hip", "fs_sched_common.h"],
+    # the dominant kernel of the stage, k_schedule_pool, and the headers it includes
+    "schedule": ["fs_sched_onchip.hip", "fs_sched_pool.h", "fs_sched_common.h"],
     "metrics": ["fs_metrics.hip"],
     "history": ["fs_history.hip"],
     "workload": ["fs_workload.hip"],

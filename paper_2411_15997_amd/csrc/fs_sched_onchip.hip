@@ -41,32 +41,17 @@
 #include <type_traits>
 
 #include "fs_sched_global.h"
+#include "fs_sched_pool.h"
 
 namespace fs {
 namespace sched {
 namespace {
 
-constexpr int64_t kPackLimit = int64_t(1) << 40;  // costs that fit a packed request
-constexpr uint64_t kTokMask = (uint64_t(1) << 24) - 1;
 constexpr int kSlots = 64;
 constexpr uint32_t kTier1 = 0x40000000u;  // the tier bit in a key's high word
 constexpr uint32_t kValHi = 0x3fffffffu;  // the counter's bits in a key's high word
 constexpr uint32_t kRelTier1 = 0x80000000u;  // the tier bit of a relative key
 constexpr uint32_t kRelMax = 0x7fffffffu;    // largest relative counter (saturated)
-
-// window flags
-constexpr int32_t kFirst = 1;        // first call of its interaction
-constexpr int32_t kReasonShift = 1;  // bits 1-2: raw throttle reason (0 within limits)
-constexpr int32_t kHeadBlk = 8;      // later call whose interaction's first call was throttled
-constexpr int32_t kPrevAdm = 16;     // later call whose previous call has been admitted
-constexpr int32_t kBig = 32;         // cost too large for a packed request
-constexpr int32_t kPrevDrop = 64;    // later call whose previous call was dropped
-
-// A queued request on chip: record, its next call (-1: none), (cost << 24) | tokens.
-struct __align__(16) Ent {
-  int32_t rec, succ;
-  uint32_t lo, hi;
-};
 
 // A batch of arrivals, lane-parallel: a user joining Q (its id, counter, segment and
 // its batch lanes) and a ready later call (record, next call, packed request, slot).
@@ -79,39 +64,16 @@ struct __align__(16) ReadyEnt {
   uint32_t lo, hi;
   int32_t x, pad[3];
 };
+constexpr int kPoolBack = 32;  // users and ready calls with which the pool pass takes a replica back
 constexpr size_t kArriveBytes = kSlots * (sizeof(JoinEnt) + sizeof(ReadyEnt) + 4);
-
-__device__ inline Ent mk_ent(int32_t rec, int32_t sc, uint32_t lo, uint32_t hi) {
-  Ent e;
-  e.rec = rec;
-  e.succ = sc;
-  e.lo = lo;
-  e.hi = hi;
-  return e;
-}
-
-__device__ inline int32_t ff1(uint64_t m) { return __ffsll((long long)m) - 1; }
-
-// A field of the kernel's argument block, loaded with a scalar load where it is used
-// instead of being held in a scalar register for the whole kernel.  The block is the
-// kernel's only argument, at the start of the kernarg segment.
-template <class T>
-__device__ __forceinline__ T arg_at(uint32_t off) {
-  __asm__ volatile("" : "+s"(off));
-  const __attribute__((address_space(4))) char *k =
-      (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
-  return *(const __attribute__((address_space(4))) T *)(k + off);
-}
-#define KARG(f) arg_at<decltype(SchedArgs{}.f)>(uint32_t(offsetof(SchedArgs, f)))
-
-#define STATE(T, field) reinterpret_cast<T *>(KARG(state) + KARG(L.field))
 
 // FCFS: first come, first served; BLIND: interaction-blind limits; LITERAL: the literal
 // engine (the engine flags).  LINKS: the trace has interactions of several calls (its
 // call, head and prev arrays are set); without them every request is a first call, so
 // nothing is ever a ready later call and the interaction bookkeeping compiles away.
 template <bool FCFS, bool BLIND, bool LITERAL, bool LINKS>
-__device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem) {
+__device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, bool resumed = false,
+                                               int32_t stay = 0) {
   const int32_t r = blockIdx.x;
   if (*a.err) return;
   if (!state_header_ok(a)) return;
@@ -147,7 +109,10 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem) {
   int64_t debt = uni64(rs->debt), backlog = uni64(rs->backlog), gap = uni64(rs->gap);
   int64_t last_exit_u = uni64(rs->last_exit_u);
   int32_t last_exit = uni(rs->last_exit);
-  const int64_t s_end = a.n_steps < 0 ? INT64_MAX : int64_t(s) + a.n_steps;
+  // (resumed: the pool pass handed the replica over within this launch, and takes it back
+  // at the end of a step that leaves few users and ready calls, after `stay` steps)
+  const int32_t s_first = s;
+  const int64_t s_end = resumed ? uni64(rs->s_end) : a.n_steps < 0 ? INT64_MAX : int64_t(s) + a.n_steps;
   const int64_t C = a.cap, theta = a.theta;
   constexpr bool fcfs = FCFS, blind = BLIND;
   // literal engine: the running batch and the KV tokens it holds
@@ -263,7 +228,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem) {
   int64_t B = 0;      // base of the relative keys
   bool wide = false;  // some counter is 2^31 - 1 or more above B: compare full keys
   int32_t code = 0;
-  bool overflow = false, mid = false;
+  bool overflow = false, mid = false, back = false;
   int64_t mid_budget = 0;
 
   auto rel_of = [&](int64_t u) -> uint32_t {
@@ -1488,6 +1453,10 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem) {
       }
     }
     ++s;
+    if (!FCFS && !BLIND && !LITERAL && resumed && s - s_first >= stay && nX + __popcll(pocc) <= kPoolBack) {
+      back = true;
+      break;
+    }
   }
 
   if (code) raise_err(a.err, code);
@@ -1543,7 +1512,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem) {
     rs->low = low;
     rs->last_exit = last_exit;
     rs->done = drained ? 1 : 0;
-    rs->overflow = overflow ? 1 : 0;
+    rs->overflow = overflow ? 1 : (back && !drained) ? 2 : 0;
     rs->mid = mid ? 1 : 0;
     rs->mid_budget = mid_budget;
     rs->s_end = s_end;
@@ -1589,6 +1558,42 @@ __global__ void __launch_bounds__(64) k_schedule_onchip(SchedArgs a) {
     __syncthreads();
     global_replica<true, (FCFS ? 1 : 0) | (BLIND ? 2 : 0) | (LITERAL ? 4 : 0)>(ka, r, smem, true,
                                                                           ka.oc.inl_hblk);
+  }
+}
+
+// The paper's policy: the pool pass, and the pass above for a replica while it has outgrown
+// the pool (taken back when users and ready calls are down to kPoolBack, half the lanes, and
+// after a number of steps that doubles each time: a change of passes rebuilds the queue, and
+// what outgrew the pool may be more than its users, as a user's calls spilled too far apart).
+template <bool LINKS>
+__global__ void __launch_bounds__(64) k_schedule_pool(SchedArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  if (*a.err) return;
+  if (!state_header_ok(a)) return;
+  if (finish_if_done(a, blockIdx.x)) return;
+  bool resumed = false;
+  int32_t stay = 32;
+  while (true) {
+    // the arguments read afresh, so that no value of one pass stays live into the other
+    uint32_t off0 = 0;
+    __asm__ volatile("" : "+s"(off0));
+    const __attribute__((address_space(4))) char *kp =
+        (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+    const SchedArgs &ka = *(const SchedArgs *)(const __attribute__((address_space(4))) SchedArgs *)(kp + off0);
+    if (ka.oc.p_cache > 0) {
+      pool_replica<LINKS>(ka, smem, resumed);
+      wave_fence();
+      const RepState *rs = reinterpret_cast<const RepState *>(ka.state + ka.L.reps) + blockIdx.x;
+      if (uni(ld_fresh(&rs->overflow)) != 1) return;
+      __syncthreads();
+      resumed = true;
+    }
+    stay = stay < (1 << 28) ? stay * 2 : stay;
+    onchip_replica<false, false, false, LINKS>(ka, smem, resumed, stay);
+    wave_fence();
+    const RepState *rs = reinterpret_cast<const RepState *>(ka.state + ka.L.reps) + blockIdx.x;
+    if (!resumed || uni(ld_fresh(&rs->overflow)) != 2) return;
+    __syncthreads();
   }
 }
 
@@ -1645,6 +1650,42 @@ OnchipCfg onchip_config(int32_t R, int32_t U, bool literal) {
   return c;
 }
 
+// LDS of the pool pass, from the same budget per work-group: the counters of idle users
+// and the table that matches a window's users when they fit in a quarter each, the spill
+// links in up to two fifths of the rest (4,096 records on the weight sweep's 39 KB), and
+// the arrival cache.  User ids share a word with the position in the pool: 26 bits.
+void pool_config(int32_t R, int32_t U, OnchipCfg &c) {
+  c.p_cache = c.p_links = c.p_users = c.p_tab = 0;
+  if (U > (1 << (32 - kAheadBits))) return;
+  const int per_cu = R <= 256 ? 1 : R <= 512 ? 2 : R <= 768 ? 3 : 4;
+  size_t budget = size_t(160 * 1024) / per_cu - 1024;
+  const size_t dev_max = size_t(max_lds_per_block());
+  if (budget > dev_max) budget = dev_max;
+  c.p_users = size_t(U) * 8 <= budget / 4 ? 1 : 0;
+  const size_t users = c.p_users ? size_t(U) * 8 : 0;
+  int tab = 64;  // power of two, at least U while it fits
+  while (tab < U && tab < 32768 && size_t(tab) * 2 <= budget / 4) tab <<= 1;
+  c.p_tab = tab;
+  const size_t left = budget - PoolLds::end - kStPad - users - size_t(tab);
+  int links = 16384;
+  while (links > 256 && size_t(links) * 2 > left * 2 / 5) links >>= 1;
+  c.p_links = links;
+  int cache = 4096;
+  while (cache > 64 && size_t(cache) * (sizeof(Ent) + 1) > left - size_t(links) * 2) cache >>= 1;
+  c.p_cache = cache;
+  const size_t total = PoolLds::end + kStPad + size_t(cache) * (sizeof(Ent) + 1) + users + size_t(links) * 2 + size_t(tab);
+  if (total > c.lds_bytes) c.lds_bytes = total;
+}
+
+template <bool LINKS>
+void launch_pool(SchedArgs a, hipStream_t s) {
+  pool_config(a.t.R, a.t.U, a.oc);
+  const void *k = reinterpret_cast<const void *>(&k_schedule_pool<LINKS>);
+  if (a.oc.lds_bytes > 65536)
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, int(a.oc.lds_bytes));
+  hipLaunchKernelGGL((k_schedule_pool<LINKS>), dim3(a.t.R), dim3(64), a.oc.lds_bytes, s, a);
+}
+
 template <bool FCFS, bool BLIND, bool LITERAL, bool LINKS>
 void launch_links(const SchedArgs &a, hipStream_t s) {
   const void *k = reinterpret_cast<const void *>(&k_schedule_onchip<FCFS, BLIND, LITERAL, LINKS>);
@@ -1664,8 +1705,12 @@ template <bool LITERAL>
 void launch_engine(const SchedArgs &a, hipStream_t s) {
   if (a.fcfs)
     a.blind ? launch_mode<true, true, LITERAL>(a, s) : launch_mode<true, false, LITERAL>(a, s);
+  else if (a.blind)
+    launch_mode<false, true, LITERAL>(a, s);
+  else if constexpr (LITERAL)
+    launch_mode<false, false, LITERAL>(a, s);
   else
-    a.blind ? launch_mode<false, true, LITERAL>(a, s) : launch_mode<false, false, LITERAL>(a, s);
+    a.t.call ? launch_pool<true>(a, s) : launch_pool<false>(a, s);
 }
 
 void launch_onchip(const SchedArgs &a, hipStream_t s) {

@@ -1,0 +1,61 @@
+"""Parity of the scheduler's pool pass (one queued call per lane) with the oracle at the
+edges of its capacities: 64 calls, 64 users, spilled first calls and the reach of their
+links, chains whose next call waits, ties of zero-cost calls, keys too far apart for one
+order word, and the hand-over to the slot pass and back; in one call and in slices."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import compare_sim, gpu_schedule, say
+from tiny import random_trace
+import tracegen as tg
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(tr, cost, reason, step, cap, theta, chunks):
+    o = oracle.simulate(tr, cost, reason, step, cap, theta)
+    compare_sim(gpu_schedule(tr, cost, reason, step, cap, theta), o)
+    compare_sim(gpu_schedule(tr, cost, reason, step, cap, theta, chunks=chunks), o)
+
+
+@pytest.mark.parametrize("multi", [False, True])
+@pytest.mark.parametrize("users,cap,theta", [(3, 20, 10 ** 9), (40, 25, 300), (63, 60, 10 ** 9),
+                                             (64, 30, 500), (66, 45, 10 ** 9), (130, 25, 10 ** 9),
+                                             (200_000, 30, 400)])
+def test_pool_edges(users, cap, theta, multi):
+    """Backlogs of a few users with long queues up to more users than lanes."""
+    rng = np.random.default_rng(users * 2 + multi)
+    say("pool edges", users, cap, theta, multi)
+    tr = tg.concat([random_trace(rng, 1500, users, 2, 4000, multi=multi, max_tok=8) for _ in range(3)])
+    for most in (2, 5000, 1 << 39):   # ties, plain, far-apart keys
+        cost = rng.integers(0, most, tr.n).astype(np.int64)
+        reason = rng.integers(0, 3, tr.n).astype(np.uint8)
+        _check(tr, cost, reason, 50, cap, theta, 23)
+
+
+@pytest.mark.parametrize("multi", [False, True])
+@pytest.mark.parametrize("replicas,n", [(1, 20_000), (800, 60), (1, 300)])
+def test_pool_spilled_calls(replicas, n, multi):
+    """A queue longer than the pool (its tail is spilled), and longer than the links reach."""
+    rng = np.random.default_rng(n + multi)
+    say("pool spill", replicas, n, multi)
+    tr = tg.concat([random_trace(rng, n, 2, 2, n // 2 + 1, multi=multi, max_tok=8)
+                    for _ in range(replicas)])
+    cost = rng.integers(0, 4000, tr.n).astype(np.int64)
+    reason = np.zeros(tr.n, np.uint8)
+    _check(tr, cost, reason, 10, 30, 10 ** 9, 400)
+
+
+def test_pool_outgrown_and_taken_back():
+    """Bursts of more users than lanes between quiet stretches: the replica changes passes
+    and comes back; users are lifted, throttled and chained across the changes."""
+    rng = np.random.default_rng(9)
+    tr = random_trace(rng, 6000, 150, 2, 100, multi=True, max_tok=6)
+    tr.ts_us = np.sort(np.concatenate([np.full(120, b * 40_000) + rng.integers(0, 600, 120)
+                                       for b in range(50)])).astype(np.int64)
+    cost = rng.integers(0, 900, tr.n).astype(np.int64)
+    reason = rng.integers(0, 3, tr.n).astype(np.uint8)
+    for theta in (10 ** 9, 200, -1):
+        say("pool taken back", theta)
+        _check(tr, cost, reason, 100, 12, theta, 301)
