@@ -6,6 +6,8 @@
 // Each replica's total charged service is also summed exactly (the low and high 32-bit
 // halves of every admitted cost in two 64-bit counters): at 2^62 or more the call
 // reports an overflow, and below that no per-user sum can wrap.
+#include <algorithm>
+
 #include "fs_device.h"
 #include "fs_launch.h"
 
@@ -53,6 +55,9 @@ struct MArgs {
   unsigned long long *counters;
   fs_metrics m;
   int32_t *err;
+  int32_t chunk;               // consecutive records a work-group takes
+  unsigned long long *part;    // [R][parts][8] partial sums of the finish pass
+  int32_t parts;               // work-groups a replica's users are summed by (1: in the finish pass)
 };
 
 __global__ void k_m_zero(MArgs a, int64_t RU, int64_t N) {
@@ -97,226 +102,24 @@ __device__ inline unsigned long long wave_sum(unsigned long long v) {
   }
   return v;
 }
-__device__ inline uint32_t wave_or(uint32_t v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v |= uint32_t(__shfl_xor(int(v), m, 64));
-  return v;
-}
-
-// Per-key aggregation within a wave before touching global memory: heavy users
-// repeat many times in a wave, and all lanes usually share one replica.
-// For each distinct key among the active lanes: one atomic add (and one atomic or).
-__device__ inline void wave_add_by_key(bool active, int64_t key, unsigned long long v,
-                                       unsigned long long *sum_base, uint32_t f,
-                                       uint32_t *or_base) {
-  const int lane = threadIdx.x & 63;
-  uint64_t pending = __ballot(active);
-  while (pending) {
-    const int leader = __ffsll((long long)pending) - 1;
-    const int64_t kl = __shfl(key, leader, 64);
-    const bool mine = active && key == kl;
-    const unsigned long long total = wave_sum(mine ? v : 0ull);
-    const uint32_t flags = or_base ? wave_or(mine ? f : 0u) : 0u;
-    if (lane == leader) {
-      if (total) atomicAdd(sum_base + kl, total);
-      if (or_base && flags) atomicOr(or_base + kl, flags);
-    }
-    pending &= ~__ballot(mine);
-  }
-}
-
-// The same for keys that are mostly distinct within a wave (users): lanes of one key
-// find a representative lane through a per-wave hash table in LDS (any lane of the key
-// wins the slot), add into its LDS accumulator, and the representative issues one
-// atomic.  A lane whose key lost its slot to another key updates its own key.
-constexpr int kKeyTab = 1024;  // hash slots per wave
-struct KeyScratch {
-  uint8_t tab[kKeyTab];
-  unsigned long long acc[64];
-  uint32_t accf[64];
-};
-// (skip_set: read the flags first and skip the atomic when they are already set.)
-__device__ inline void wave_add_by_key_hashed(bool active, int64_t key, unsigned long long v,
-                                              unsigned long long *sum_base, uint32_t f,
-                                              uint32_t *or_base, KeyScratch &ks,
-                                              bool skip_set = false) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t h = (uint32_t(uint64_t(key)) * 2654435761u) >> 22;  // 10 bits
-  if (active) ks.tab[h] = uint8_t(lane);
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  const int rp = active ? int(ks.tab[h]) : lane;
-  const int64_t rk = __shfl(key, rp, 64);
-  const bool own = active && rk == key;
-  const bool lead = own && rp == lane;
-  if (lead) {
-    ks.acc[lane] = 0;
-    ks.accf[lane] = 0;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  if (own) {
-    if (v) atomicAdd(&ks.acc[rp], v);
-    if (or_base && f) atomicOr(&ks.accf[rp], f);
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  if (lead) {
-    const unsigned long long t = ks.acc[lane];
-    const uint32_t fl = ks.accf[lane];
-    if (t) atomicAdd(sum_base + key, t);
-    if (or_base && fl && !(skip_set && (or_base[key] & fl) == fl)) atomicOr(or_base + key, fl);
-  } else if (active && !own) {
-    if (v) atomicAdd(sum_base + key, v);
-    if (or_base && f && !(skip_set && (or_base[key] & f) == f)) atomicOr(or_base + key, f);
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-}
-
-// Up to three small per-replica counts (each below 2^16 in a wave) in one reduction:
-// counters[r * C_NUM + c_i] += x_i for each distinct replica r of the active lanes.
-__device__ inline void wave_count3(bool active, int32_t r, unsigned long long *counters,
-                                   int c0, uint32_t x0, int c1, uint32_t x1, int c2, uint32_t x2) {
-  const int lane = threadIdx.x & 63;
-  uint64_t pending = __ballot(active);
-  while (pending) {
-    const int leader = __ffsll((long long)pending) - 1;
-    const int32_t rl = __shfl(r, leader, 64);
-    const bool mine = active && r == rl;
-    const unsigned long long packed =
-        mine ? (uint64_t(x0) | (uint64_t(x1) << 16) | (uint64_t(x2) << 32)) : 0ull;
-    const unsigned long long total = wave_sum(packed);
-    if (lane == leader) {
-      unsigned long long *cr = counters + int64_t(rl) * C_NUM;
-      const unsigned long long t0 = total & 0xffffu, t1 = (total >> 16) & 0xffffu,
-                               t2 = (total >> 32) & 0xffffu;
-      if (c0 >= 0 && t0) atomicAdd(cr + c0, t0);
-      if (c1 >= 0 && t1) atomicAdd(cr + c1, t1);
-      if (c2 >= 0 && t2) atomicAdd(cr + c2, t2);
-    }
-    pending &= ~__ballot(mine);
-  }
-}
-
 // An admitted cost as charged service: in [0, 2^62), else a range error (not added).
 __device__ inline bool cost_ok(int64_t c) { return c >= 0 && c < kValueLimit; }
 
-// The exact per-replica total of the admitted costs: the low and high 32-bit halves of
-// each cost summed separately (neither sum can wrap: fewer than 2^31 records).
-__device__ inline void wave_cost2(bool active, int32_t r, unsigned long long *counters,
-                                  int64_t c) {
-  const int lane = threadIdx.x & 63;
-  uint64_t pending = __ballot(active && c != 0);
-  while (pending) {
-    const int leader = __ffsll((long long)pending) - 1;
-    const int32_t rl = __shfl(r, leader, 64);
-    const bool mine = active && r == rl;
-    const unsigned long long lo = wave_sum(mine ? (uint64_t(c) & 0xffffffffull) : 0ull);
-    const unsigned long long hi = wave_sum(mine ? (uint64_t(c) >> 32) : 0ull);
-    if (lane == leader) {
-      unsigned long long *cr = counters + int64_t(rl) * C_NUM;
-      if (lo) atomicAdd(cr + C_COST_LO, lo);
-      if (hi) atomicAdd(cr + C_COST_HI, hi);
-    }
-    pending &= ~__ballot(mine);
-  }
-}
-
-// The replica of record g, walking forward from the replica of the block's first
-// record (records of a replica are contiguous, so a block spans few of them).
-__device__ inline int32_t replica_from(const int64_t *rep_off, int32_t r0, int64_t g) {
-  int32_t r = r0;
-  while (__ldg(rep_off + r + 1) <= g) ++r;
-  return r;
-}
-
-// Pass 1: per record -- validity, user flags, charged service, interaction flags.
-__global__ void __launch_bounds__(256) k_m_records(MArgs a) {
-  __shared__ KeyScratch ks[4];
-  const DevTrace &t = a.t;
-  int32_t code = 0;
-  // grid-stride over whole waves so that every lane takes part in the wave reductions
-  for (int64_t base0 = blockIdx.x * int64_t(blockDim.x); base0 < t.N;
-       base0 += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t g = base0 + threadIdx.x;
-    bool ok = g < t.N;
-    int32_t r = 0, k = 0;
-    int64_t base = 0, i = 0, h = 0;
-    const int32_t r0 = replica_of(t.rep_off, t.R, base0);  // (a uniform search)
-    if (ok) {
-      r = replica_from(t.rep_off, r0, g);
-      base = t.rep_off[r];
-      i = g - base;
-      k = t.user[g];
-      if (k < 0 || k >= t.U || t.app[g] < 0 || t.app[g] >= t.A) {
-        code = max(code, int32_t(FS_E_RANGE));
-        ok = false;
-      }
-    }
-    if (ok) {
-      h = i;
-      if (!first_call(t, g)) {
-        h = t.head[g];
-        if (h < 0 || h >= i) {
-          code = max(code, int32_t(FS_E_RANGE));
-          ok = false;
-        }
-      }
-    }
-    const int8_t st = ok ? a.status[g] : int8_t(-1);
-    const bool served = ok && st == 0;
-    int64_t cg = served ? a.cost[g] : 0;
-    if (!cost_ok(cg)) {
-      code = max(code, int32_t(FS_E_RANGE));
-      cg = 0;
-    }
-    uint32_t uf = U_HAS;
-    if (served && is_delayed(a.admit_step[g], t.ts[g], a.tau, a.D)) uf |= U_DELAYED;
-    if (ok && h != i) atomicOr(a.iflags + base + h, own_iflag(st));
-    const int64_t uk = int64_t(r) * t.U + k;
-    wave_add_by_key_hashed(ok, uk, (unsigned long long)cg, a.charged, uf, a.uflags,
-                           ks[threadIdx.x >> 6]);
-    wave_count3(ok, r, a.counters, C_ADMITTED, served ? 1u : 0u, C_THROTTLED,
-                (ok && st > 0) ? 1u : 0u, C_INTERACTIONS, (ok && first_call(t, g)) ? 1u : 0u);
-    wave_cost2(ok, r, a.counters, cg);
-  }
-  if (code) raise_err(a.err, code);
-}
-
-// Pass 2: per interaction (first call) -- fully served, aborted midway.
-__global__ void __launch_bounds__(256) k_m_interactions(MArgs a) {
-  __shared__ KeyScratch ks[4];
-  const DevTrace &t = a.t;
-  for (int64_t base0 = blockIdx.x * int64_t(blockDim.x); base0 < t.N;
-       base0 += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t g = base0 + threadIdx.x;
-    bool ok = g < t.N && first_call(t, g);
-    int32_t k = ok ? t.user[g] : 0;
-    ok = ok && k >= 0 && k < t.U;
-    const int32_t r0 = replica_of(t.rep_off, t.R, base0);
-    const int32_t r = ok ? replica_from(t.rep_off, r0, g) : 0;
-    const uint32_t f = ok ? (later_iflags(a, g) | own_iflag(a.status[g])) : 0u;
-    const bool full = ok && !(f & I_UNSERVED);
-    const bool aborted = ok && (f & I_SERVED) && (f & I_UNSERVED);
-    // one flag per user and wave; a heavy user has many fully served interactions, so
-    // the atomic is skipped once its flag is visible (a stale read only costs an atomic
-    // that changes nothing)
-    wave_add_by_key_hashed(full, int64_t(r) * t.U + k, 0ull, nullptr, U_FULL, a.uflags,
-                           ks[threadIdx.x >> 6], true);
-    wave_count3(ok, r, a.counters, C_FULL, full ? 1u : 0u, C_ABORTED, aborted ? 1u : 0u, -1, 0u);
-  }
-}
-
-// Replicas whose users fit in LDS: a work-group takes kChunk consecutive records and,
+// Replicas whose users fit in LDS: a work-group takes a chunk of consecutive records and,
 // for each replica segment among them, sums the charged service and ORs the user
 // flags in LDS tables indexed by user, then adds each touched user's values to global
 // memory once.  Per-replica counts are reduced over the work-group.
-constexpr int kChunk = 8192;
+constexpr int kChunk = 8192;      // at most
+constexpr int kChunkLeast = 1024;
 constexpr int kLdsUsers = 4096;
 
-// Sums three per-thread counts over the work-group (256 threads) and adds them to the
+// Sums three per-thread counts over the work-group (NW waves) and adds them to the
 // replica's counters c0, c1, c2 (c < 0: unused).
 // (c0b >= 0: x0's total also goes to counter c0b)
+template <int NW = 4>
 __device__ inline void block_count3(uint32_t x0, uint32_t x1, uint32_t x2,
                                     unsigned long long *cr, int c0, int c1, int c2,
-                                    unsigned long long (*s_red)[4], int c0b = -1) {
+                                    unsigned long long (*s_red)[NW], int c0b = -1) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const unsigned long long packed =
       uint64_t(x0) | (uint64_t(x1) << 21) | (uint64_t(x2) << 42);  // each at most kChunk
@@ -324,7 +127,8 @@ __device__ inline void block_count3(uint32_t x0, uint32_t x1, uint32_t x2,
   if (lane == 0) s_red[0][wave] = tw;
   __syncthreads();
   if (threadIdx.x == 0) {
-    const unsigned long long t = s_red[0][0] + s_red[0][1] + s_red[0][2] + s_red[0][3];
+    unsigned long long t = 0;
+    for (int w = 0; w < NW; ++w) t += s_red[0][w];
     const unsigned long long m = (uint64_t(1) << 21) - 1;
     if (c0 >= 0 && (t & m)) atomicAdd(cr + c0, t & m);
     if (c0b >= 0 && (t & m)) atomicAdd(cr + c0b, t & m);
@@ -335,8 +139,9 @@ __device__ inline void block_count3(uint32_t x0, uint32_t x1, uint32_t x2,
 
 // Adds the work-group's sums of the admitted costs' low and high halves to the
 // replica's counters (each block sum is below 2^45).
+template <int NW = 4>
 __device__ inline void block_cost2(unsigned long long lo, unsigned long long hi,
-                                   unsigned long long *cr, unsigned long long (*s_red)[4]) {
+                                   unsigned long long *cr, unsigned long long (*s_red)[NW]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const unsigned long long tl = wave_sum(lo), th = wave_sum(hi);
   if (lane == 0) {
@@ -345,8 +150,11 @@ __device__ inline void block_cost2(unsigned long long lo, unsigned long long hi,
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const unsigned long long l = s_red[0][0] + s_red[0][1] + s_red[0][2] + s_red[0][3];
-    const unsigned long long h = s_red[1][0] + s_red[1][1] + s_red[1][2] + s_red[1][3];
+    unsigned long long l = 0, h = 0;
+    for (int w = 0; w < NW; ++w) {
+      l += s_red[0][w];
+      h += s_red[1][w];
+    }
     if (l) atomicAdd(cr + C_COST_LO, l);
     if (h) atomicAdd(cr + C_COST_HI, h);
   }
@@ -360,8 +168,8 @@ __global__ void __launch_bounds__(256) k_m_records_lds(MArgs a) {
   const DevTrace &t = a.t;
   unsigned long long *const s_chg = s_dyn;
   uint32_t *const s_uf = reinterpret_cast<uint32_t *>(s_dyn + t.U);
-  const int64_t c0 = blockIdx.x * int64_t(kChunk);
-  const int64_t c1 = c0 + kChunk < t.N ? c0 + kChunk : t.N;
+  const int64_t c0 = blockIdx.x * int64_t(a.chunk);
+  const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
   int32_t r = replica_of(t.rep_off, t.R, c0);
   int32_t code = 0;
   for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
@@ -454,8 +262,8 @@ __global__ void __launch_bounds__(256) k_m_interactions_lds(MArgs a) {
   __shared__ unsigned long long s_red[2][4];
   const DevTrace &t = a.t;
   uint8_t *const s_full = reinterpret_cast<uint8_t *>(s_dyn);
-  const int64_t c0 = blockIdx.x * int64_t(kChunk);
-  const int64_t c1 = c0 + kChunk < t.N ? c0 + kChunk : t.N;
+  const int64_t c0 = blockIdx.x * int64_t(a.chunk);
+  const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
   int32_t r = replica_of(t.rep_off, t.R, c0);
   for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
     while (t.rep_off[r + 1] <= s0) ++r;
@@ -482,14 +290,192 @@ __global__ void __launch_bounds__(256) k_m_interactions_lds(MArgs a) {
   }
 }
 
+// More users than an LDS table holds: a work-group's chunk goes through an LDS hash table
+// keyed by (replica, user), so that each user it meets reaches global memory once (a
+// heavy user of one replica is in most chunks, thousands of times in each), and the
+// per-replica counts are reduced over the work-group.  One replica's counters and its
+// heaviest user are single addresses: with one atomic a wave on them the two passes over
+// 10M requests of 100,000 users took 7.7 and 1.9 ms, the atomics of 156,000 waves on one
+// line at 6-10 ns each.  What is left is bound by the atomics of the tables' entries, about
+// 15 G/s over the chip, so a work-group takes as many records as its table of 8,192 users
+// holds, one work-group a CU: 1.2M entries over those 10M requests, where chunks of 8,192
+// records make 1.9M.
+constexpr int kHashThreads = 1024;
+constexpr int kHashWaves = kHashThreads / 64;
+constexpr int kHashBits = 13;
+constexpr int kHashSlots = 1 << kHashBits;
+constexpr int kHashChunk = 40960;  // records of a work-group, at most
+constexpr int kHashProbes = 8;
+constexpr uint32_t kHashEmpty = 0xffffffffu;  // (a key is below R * U <= 2^31)
+
+struct HashLds {
+  unsigned long long sum[kHashSlots];
+  uint32_t key[kHashSlots], flag[kHashSlots];
+  unsigned long long red[2][kHashWaves];
+};
+
+__device__ inline uint32_t hash_slot(uint32_t key) { return (key * 2654435761u) >> (32 - kHashBits); }
+
+__global__ void __launch_bounds__(kHashThreads) k_m_records_hash(MArgs a) {
+  extern __shared__ __align__(16) unsigned char m_smem[];
+  HashLds &sm = *reinterpret_cast<HashLds *>(m_smem);
+  const DevTrace &t = a.t;
+  for (int k = threadIdx.x; k < kHashSlots; k += kHashThreads) {
+    sm.sum[k] = 0;
+    sm.key[k] = kHashEmpty;
+    sm.flag[k] = 0;
+  }
+  __syncthreads();
+  const int64_t c0 = blockIdx.x * int64_t(a.chunk);
+  const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
+  int32_t r = replica_of(t.rep_off, t.R, c0);
+  int32_t code = 0;
+  for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
+    while (t.rep_off[r + 1] <= s0) ++r;  // (empty replicas)
+    const int64_t base = t.rep_off[r];
+    const int64_t s1 = t.rep_off[r + 1] < c1 ? t.rep_off[r + 1] : c1;
+    uint32_t n_adm = 0, n_thr = 0, n_int = 0;
+    unsigned long long c_lo = 0, c_hi = 0;
+    for (int64_t g0 = s0 + threadIdx.x; g0 < s1; g0 += kRecBatch * kHashThreads) {
+      int32_t uk[kRecBatch], ap[kRecBatch], cl[kRecBatch], hd[kRecBatch], as[kRecBatch];
+      int8_t st[kRecBatch];
+      int64_t ts[kRecBatch], cs[kRecBatch];
+#pragma unroll
+      for (int j = 0; j < kRecBatch; ++j) {
+        const int64_t g = g0 + j * kHashThreads;
+        const bool v = g < s1;
+        uk[j] = v ? t.user[g] : 0;
+        ap[j] = v ? t.app[g] : 0;
+        cl[j] = (v && t.call) ? t.call[g] : 0;
+        hd[j] = (v && t.call) ? t.head[g] : 0;
+        st[j] = v ? a.status[g] : int8_t(-1);
+        as[j] = v ? a.admit_step[g] : 0;
+        ts[j] = v ? t.ts[g] : 0;
+        cs[j] = v ? a.cost[g] : 0;
+      }
+#pragma unroll
+      for (int j = 0; j < kRecBatch; ++j) {
+        const int64_t g = g0 + j * kHashThreads;
+        if (g >= s1) continue;
+        const int64_t i = g - base;
+        bool ok = uk[j] >= 0 && uk[j] < t.U && ap[j] >= 0 && ap[j] < t.A;
+        const bool fc = cl[j] == 0;
+        int64_t h = i;
+        if (ok && !fc) {
+          h = hd[j];
+          ok = h >= 0 && h < i;
+        }
+        if (!ok) {
+          code = int32_t(FS_E_RANGE);
+          continue;
+        }
+        const bool served = st[j] == 0;
+        uint32_t uf = U_HAS;
+        if (served && is_delayed(as[j], ts[j], a.tau, a.D)) uf |= U_DELAYED;
+        if (served && !t.call) uf |= U_FULL;
+        if (!fc) atomicOr(a.iflags + base + h, own_iflag(st[j]));
+        unsigned long long c = 0;
+        if (served && !cost_ok(cs[j])) {
+          code = int32_t(FS_E_RANGE);
+        } else if (served) {
+          c = (unsigned long long)cs[j];
+          c_lo += c & 0xffffffffull;
+          c_hi += c >> 32;
+        }
+        n_adm += served ? 1u : 0u;
+        n_thr += st[j] > 0 ? 1u : 0u;
+        n_int += fc ? 1u : 0u;
+        const uint32_t key = uint32_t(int64_t(r) * t.U + uk[j]);
+        uint32_t s = hash_slot(key);
+        int p = 0;
+        for (; p < kHashProbes; ++p, s = (s + 1) & (kHashSlots - 1)) {
+          uint32_t k = sm.key[s];
+          if (k == kHashEmpty) k = atomicCAS(&sm.key[s], kHashEmpty, key);
+          if (k == kHashEmpty || k == key) break;
+        }
+        if (p < kHashProbes) {
+          if (c) atomicAdd(&sm.sum[s], c);
+          if ((sm.flag[s] & uf) != uf) atomicOr(&sm.flag[s], uf);
+        } else {  // (the table is full around the slot)
+          if (c) atomicAdd(a.charged + key, c);
+          if ((a.uflags[key] & uf) != uf) atomicOr(a.uflags + key, uf);
+        }
+      }
+    }
+    unsigned long long *const cr = a.counters + int64_t(r) * C_NUM;
+    block_count3<kHashWaves>(n_adm, n_thr, n_int, cr, C_ADMITTED, C_THROTTLED, C_INTERACTIONS, sm.red,
+                             t.call ? -1 : int(C_FULL));
+    __syncthreads();
+    block_cost2<kHashWaves>(c_lo, c_hi, cr, sm.red);
+    __syncthreads();
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < kHashSlots; k += kHashThreads) {
+    const uint32_t key = sm.key[k];
+    if (key == kHashEmpty) continue;
+    const uint32_t f = sm.flag[k];
+    if (sm.sum[k]) atomicAdd(a.charged + key, sm.sum[k]);
+    if ((a.uflags[key] & f) != f) atomicOr(a.uflags + key, f);
+  }
+  if (code) raise_err(a.err, code);
+}
+
+// Pass 2 with many users: a fully served interaction sets its user's flag once per
+// work-group (a direct-mapped table of the users already seen) and only when the flag is
+// not yet visible.
+__global__ void __launch_bounds__(kHashThreads) k_m_interactions_hash(MArgs a) {
+  __shared__ uint32_t s_seen[kHashSlots];
+  __shared__ unsigned long long s_red[2][kHashWaves];
+  const DevTrace &t = a.t;
+  for (int k = threadIdx.x; k < kHashSlots; k += kHashThreads) s_seen[k] = kHashEmpty;
+  __syncthreads();
+  const int64_t c0 = blockIdx.x * int64_t(a.chunk);
+  const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
+  int32_t r = replica_of(t.rep_off, t.R, c0);
+  for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
+    while (t.rep_off[r + 1] <= s0) ++r;
+    const int64_t s1 = t.rep_off[r + 1] < c1 ? t.rep_off[r + 1] : c1;
+    uint32_t n_full = 0, n_ab = 0;
+    for (int64_t g0 = s0 + threadIdx.x; g0 < s1; g0 += kRecBatch * kHashThreads) {
+      int32_t uk[kRecBatch];
+      uint32_t f[kRecBatch];
+      bool ok[kRecBatch];
+#pragma unroll
+      for (int j = 0; j < kRecBatch; ++j) {
+        const int64_t g = g0 + j * kHashThreads;
+        ok[j] = g < s1 && first_call(t, g);
+        uk[j] = g < s1 ? t.user[g] : -1;
+        f[j] = g < s1 ? (later_iflags(a, g) | own_iflag(a.status[g])) : 0u;
+      }
+#pragma unroll
+      for (int j = 0; j < kRecBatch; ++j) {
+        if (!ok[j] || uk[j] < 0 || uk[j] >= t.U) continue;
+        const bool full = !(f[j] & I_UNSERVED);
+        n_full += full ? 1u : 0u;
+        n_ab += ((f[j] & I_SERVED) && (f[j] & I_UNSERVED)) ? 1u : 0u;
+        if (!full) continue;
+        const uint32_t key = uint32_t(int64_t(r) * t.U + uk[j]);
+        const uint32_t s = hash_slot(key);
+        // (the exchange lets one of the user's lanes go on, and again after another user)
+        if (s_seen[s] == key || atomicExch(&s_seen[s], key) == key) continue;
+        if (!(a.uflags[key] & U_FULL))  // (a stale value only costs an atomic)
+          atomicOr(a.uflags + key, uint32_t(U_FULL));
+      }
+    }
+    block_count3<kHashWaves>(n_full, n_ab, 0, a.counters + int64_t(r) * C_NUM, C_FULL, C_ABORTED, -1,
+                             s_red);
+    __syncthreads();
+  }
+}
+
 // Pass 3: per admitted record of an aborted interaction -- wasted tokens.  Chunked like
 // the LDS passes; a replica segment without aborted interactions (every replica under
 // the paper's policy) is skipped without reading its records.
 __global__ void __launch_bounds__(256) k_m_wasted(MArgs a) {
   __shared__ unsigned long long s_red[1][4];
   const DevTrace &t = a.t;
-  const int64_t c0 = blockIdx.x * int64_t(kChunk);
-  const int64_t c1 = c0 + kChunk < t.N ? c0 + kChunk : t.N;
+  const int64_t c0 = blockIdx.x * int64_t(a.chunk);
+  const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
   int32_t r = replica_of(t.rep_off, t.R, c0);
   for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
     while (t.rep_off[r + 1] <= s0) ++r;
@@ -531,45 +517,84 @@ __device__ inline double to_double(U128 v) {
   return double(v.hi) * 18446744073709551616.0 + double(v.lo);
 }
 
-// Pass 4: one block per replica -- Jain's index and the percentages.
-__global__ void __launch_bounds__(256) k_m_finish(MArgs a) {
-  const int32_t r = blockIdx.x;
-  const int32_t U = a.t.U;
-  __shared__ U128 s1s[256], s2s[256];
-  __shared__ unsigned long long cnt[256][3];
+// The sums over a replica's users that pass 4 needs, of the thread's share of [k0, k1).
+struct UserSums {
   U128 s1 = {0, 0}, s2 = {0, 0};
-  unsigned long long users = 0, full = 0, delayed = 0;
-  for (int32_t k = threadIdx.x; k < U; k += blockDim.x) {
-    int64_t uk = int64_t(r) * U + k;
-    uint32_t f = a.uflags[uk];
+  unsigned long long cnt[3] = {0, 0, 0};  // users with a request, fully served, delayed
+};
+__device__ inline UserSums user_sums(const MArgs &a, int32_t r, int32_t k0, int32_t k1) {
+  UserSums u;
+  for (int32_t k = k0 + threadIdx.x; k < k1; k += blockDim.x) {
+    const int64_t uk = int64_t(r) * a.t.U + k;
+    const uint32_t f = a.uflags[uk];
+    const unsigned long long x = a.charged[uk];
     if (!(f & U_HAS)) continue;
-    unsigned long long x = a.charged[uk];
-    users += 1;
-    full += (f & U_FULL) ? 1 : 0;
-    delayed += (f & U_DELAYED) ? 1 : 0;
-    s1 = add128(s1, U128{x, 0});
-    U128 sq{x * x, __umul64hi(x, x)};
-    s2 = add128(s2, sq);
+    u.cnt[0] += 1;
+    u.cnt[1] += (f & U_FULL) ? 1 : 0;
+    u.cnt[2] += (f & U_DELAYED) ? 1 : 0;
+    u.s1 = add128(u.s1, U128{x, 0});
+    const U128 sq{x * x, __umul64hi(x, x)};
+    u.s2 = add128(u.s2, sq);
   }
-  s1s[threadIdx.x] = s1;
-  s2s[threadIdx.x] = s2;
-  cnt[threadIdx.x][0] = users;
-  cnt[threadIdx.x][1] = full;
-  cnt[threadIdx.x][2] = delayed;
+  return u;
+}
+struct SumsLds {
+  U128 s1[256], s2[256];
+  unsigned long long cnt[256][3];
+};
+// The work-group's total (256 threads), left in entry 0.
+__device__ inline void block_sums(const UserSums &u, SumsLds &sm) {
+  sm.s1[threadIdx.x] = u.s1;
+  sm.s2[threadIdx.x] = u.s2;
+  for (int c = 0; c < 3; ++c) sm.cnt[threadIdx.x][c] = u.cnt[c];
   __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
+  for (int w = 128; w > 0; w >>= 1) {
     if (threadIdx.x < w) {
-      s1s[threadIdx.x] = add128(s1s[threadIdx.x], s1s[threadIdx.x + w]);
-      s2s[threadIdx.x] = add128(s2s[threadIdx.x], s2s[threadIdx.x + w]);
-      for (int c = 0; c < 3; ++c) cnt[threadIdx.x][c] += cnt[threadIdx.x + w][c];
+      sm.s1[threadIdx.x] = add128(sm.s1[threadIdx.x], sm.s1[threadIdx.x + w]);
+      sm.s2[threadIdx.x] = add128(sm.s2[threadIdx.x], sm.s2[threadIdx.x + w]);
+      for (int c = 0; c < 3; ++c) sm.cnt[threadIdx.x][c] += sm.cnt[threadIdx.x + w][c];
     }
     __syncthreads();
   }
+}
+
+// The users of a replica in a.parts work-groups (many users of few replicas: one work-group
+// over 100,000 users took 230 us), each one's sums to its row.
+__global__ void __launch_bounds__(256) k_m_user_parts(MArgs a) {
+  __shared__ SumsLds sm;
+  const int32_t r = blockIdx.x / a.parts, p = blockIdx.x % a.parts;
+  const int32_t per = (a.t.U + a.parts - 1) / a.parts;
+  const int32_t k0 = p * per, k1 = k0 + per < a.t.U ? k0 + per : a.t.U;
+  block_sums(user_sums(a, r, k0, k1), sm);
+  if (threadIdx.x == 0) {
+    unsigned long long *const o = a.part + int64_t(blockIdx.x) * 8;
+    o[0] = sm.s1[0].lo;
+    o[1] = sm.s1[0].hi;
+    o[2] = sm.s2[0].lo;
+    o[3] = sm.s2[0].hi;
+    for (int c = 0; c < 3; ++c) o[4 + c] = sm.cnt[0][c];
+  }
+}
+
+// Pass 4: one block per replica -- Jain's index and the percentages.
+__global__ void __launch_bounds__(256) k_m_finish(MArgs a) {
+  const int32_t r = blockIdx.x;
+  __shared__ SumsLds sm;
+  UserSums u;
+  if (a.parts == 1) {
+    u = user_sums(a, r, 0, a.t.U);
+  } else if (int(threadIdx.x) < a.parts) {
+    const unsigned long long *const o = a.part + (int64_t(r) * a.parts + threadIdx.x) * 8;
+    u.s1 = U128{o[0], o[1]};
+    u.s2 = U128{o[2], o[3]};
+    for (int c = 0; c < 3; ++c) u.cnt[c] = o[4 + c];
+  }
+  block_sums(u, sm);
   if (threadIdx.x == 0) {
     const unsigned long long *C = a.counters + r * C_NUM;
     const int64_t n = a.t.rep_off[r + 1] - a.t.rep_off[r];
-    U128 S1 = s1s[0], S2 = s2s[0];
-    const unsigned long long nu = cnt[0][0];
+    U128 S1 = sm.s1[0], S2 = sm.s2[0];
+    const unsigned long long nu = sm.cnt[0][0];
     // the exact total charged service: hi * 2^32 + lo
     const unsigned long long lo = C[C_COST_LO], hi = C[C_COST_HI];
     if ((hi >> 30) != 0 || ((hi << 32) + lo) < (hi << 32) ||
@@ -587,8 +612,8 @@ __global__ void __launch_bounds__(256) k_m_finish(MArgs a) {
     a.m.max_gap_tokens[r] = double(a.max_gap[r]) / 65536.0;
     a.m.svc_req_pct[r] = pct(C[C_ADMITTED], (unsigned long long)n);
     a.m.svc_int_pct[r] = pct(C[C_FULL], C[C_INTERACTIONS]);
-    a.m.served_users_pct[r] = pct(cnt[0][1], nu);
-    a.m.delayed_users_pct[r] = pct(cnt[0][2], nu);
+    a.m.served_users_pct[r] = pct(sm.cnt[0][1], nu);
+    a.m.delayed_users_pct[r] = pct(sm.cnt[0][2], nu);
     a.m.throttled[r] = int64_t(C[C_THROTTLED]);
     a.m.aborted_midway[r] = int64_t(C[C_ABORTED]);
     a.m.wasted_tokens[r] = int64_t(C[C_WASTED]);
@@ -628,18 +653,42 @@ hipError_t launch_metrics(const fs_trace *t, const int64_t *cost, const fs_outpu
   const int64_t RU = int64_t(t->n_replicas) * t->n_users;
   const int64_t N = a.t.N;
   hipLaunchKernelGGL(k_m_zero, dim3(grid_for(RU > N ? RU : N, 256)), dim3(256), 0, s, a, RU, N);
+  // The finish pass in parts of at least 2,048 users, up to 256 a replica and about 1,024
+  // work-groups, when the rows fit where the interaction flags were (not read any more).
+  a.part = reinterpret_cast<unsigned long long *>(a.iflags);
+  a.parts = 1;
+  {
+    int64_t parts = std::min<int64_t>(t->n_users / 2048, 256);
+    parts = std::min<int64_t>(parts, std::max<int64_t>(1024 / t->n_replicas, 1));
+    if (parts > 1 && size_t(t->n_replicas) * size_t(parts) * 64 <= size_t(N) * 4) a.parts = int32_t(parts);
+  }
+  // Chunks of kChunk records, less when they would leave the chip idle (four a CU); the
+  // tables are cleared and added once per chunk.
+  a.chunk = int32_t(std::min<int64_t>(kChunk, std::max<int64_t>(kChunkLeast, (N / 1024 + 255) / 256 * 256)));
   if (N > 0) {
-    const int64_t chunks = (N + kChunk - 1) / kChunk;
+    const int64_t chunks = (N + a.chunk - 1) / a.chunk;
     if (t->n_users <= kLdsUsers) {
       hipLaunchKernelGGL(k_m_records_lds, dim3(chunks), dim3(256), size_t(t->n_users) * 12, s, a);
       if (t->call)  // (without links the records pass counts the fully served interactions)
         hipLaunchKernelGGL(k_m_interactions_lds, dim3(chunks), dim3(256), size_t(t->n_users), s, a);
     } else {
-      hipLaunchKernelGGL(k_m_records, dim3(grid_for(N, 256)), dim3(256), 0, s, a);
-      hipLaunchKernelGGL(k_m_interactions, dim3(grid_for(N, 256)), dim3(256), 0, s, a);
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_m_records_hash),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, int(sizeof(HashLds)));
+      const int32_t chunk = a.chunk;
+      // a whole number of work-groups a CU, each of at most kHashChunk records
+      const int64_t rounds = (N + int64_t(kHashChunk) * 256 - 1) / (int64_t(kHashChunk) * 256);
+      const int64_t per = (N + rounds * 256 - 1) / (rounds * 256);
+      a.chunk = int32_t(std::max<int64_t>((per + 255) / 256 * 256, 2048));
+      const int64_t groups = (N + a.chunk - 1) / a.chunk;
+      hipLaunchKernelGGL(k_m_records_hash, dim3(groups), dim3(kHashThreads), sizeof(HashLds), s, a);
+      if (t->call)
+        hipLaunchKernelGGL(k_m_interactions_hash, dim3(groups), dim3(kHashThreads), 0, s, a);
+      a.chunk = chunk;
     }
     hipLaunchKernelGGL(k_m_wasted, dim3(chunks), dim3(256), 0, s, a);
   }
+  if (a.parts > 1)
+    hipLaunchKernelGGL(k_m_user_parts, dim3(t->n_replicas * a.parts), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_m_finish, dim3(t->n_replicas), dim3(256), 0, s, a);
   return hipGetLastError();
 }
