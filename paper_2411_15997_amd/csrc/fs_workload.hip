@@ -4,14 +4,16 @@
 // the graph-size table (Table 2).  HBM-bound streaming passes; every accumulation is
 // an integer atomic (order-independent, so results are deterministic), aggregated per
 // wave over the lanes that share a key before it reaches memory.
-//   1. k_ws_records   per request: validity, the replica's latest arrival, requests and
+//   1. k_ws_records_hash (k_ws_records for many apps)
+//                     per request: validity, the replica's latest arrival, requests and
 //                     tokens per (replica, user, app), the length histograms and sums per
 //                     (replica, app) (in LDS per work-group and replica segment), and one
 //                     count at the interaction's first call
 //   2. k_ws_graph     per request: its interaction's size (the count at its first call)
 //                     gives its Table 2 row; first calls add to the size histogram (both
 //                     in LDS per work-group and replica segment)
-//   3. k_ws_users     per (replica, user) and per (replica, user, app): the rate bins
+//   3. k_ws_users_lds (k_ws_users for many apps)
+//                     per (replica, user) and per (replica, user, app): the rate bins
 #include "fs_device.h"
 #include "fs_launch.h"
 
@@ -29,6 +31,7 @@ struct WsArgs {
   unsigned int *size;                   // [N] records per first call
   unsigned long long *max_ts;           // [R]
   int32_t *err;
+  int32_t chunk;                        // consecutive records a work-group takes
 };
 
 __device__ inline unsigned long long wsum64(unsigned long long v) {
@@ -104,39 +107,183 @@ __global__ void __launch_bounds__(kThreads) k_ws_zero(WsArgs a, int64_t RUA, int
   (void)RU;
 }
 
-// Records are taken in chunks of kChunk consecutive requests per work-group; within a
-// chunk, each replica segment accumulates its per-application histograms and sums in
-// LDS (when the apps fit, kLdsApps) and adds each nonzero entry to global memory once.
-constexpr int kChunk = 8192;
+// Records are taken in chunks of consecutive requests per work-group (at most kChunk, fewer
+// when that would leave the chip idle); within a chunk, each replica segment accumulates
+// its per-application histograms and sums in LDS (when the apps fit, kLdsApps) and adds
+// each nonzero entry to global memory once.
+constexpr int kChunk = 8192, kChunkLeast = 1024;
 constexpr int kLdsApps = 64;
 
-struct RecLds {
-  uint32_t lh[kLdsApps * 3 * kLenBins];     // length histograms [A][3][bins]
-  unsigned long long ls[kLdsApps * 3];      // length sums [A][3]
-  unsigned long long red[kThreads / 64];    // per-wave maxima
-};
+// The records pass with the chunk's (replica, user, app) requests and tokens in an LDS hash
+// table, so that each one reaches global memory once a chunk, and the apps' length
+// histograms and sums in copies chosen by lane (a wave's lanes meet on few of their
+// entries).  Taking a wave's keys one after the other, a reduction over 64 lanes each,
+// took 3.8 ms over 10M requests of 100,000 users and 32 apps (about 50 distinct keys a wave).
+// The table's entries end in two atomics each, at about 15 G/s over the chip (390 us of the
+// 600 with chunks of 8,192 records), so a work-group takes as many records as a table of
+// 8,192 entries holds, one work-group a CU.
+constexpr int kRecThreads = 1024;
+constexpr int kRecBits = 13;
+constexpr int kRecSlots = 1 << kRecBits;
+constexpr int kRecProbes = 8;
+constexpr int kRecChunk = 40960;  // records of a work-group, at most
+constexpr int kRecApps = 64;      // applications whose tables fit beside the entries, in two copies
+                                  // up to half as many
+constexpr uint32_t kRecEmpty = 0xffffffffu;  // (a key is below R * U * A, which is checked)
 
-template <bool LDS>
-__global__ void __launch_bounds__(kThreads) k_ws_records(WsArgs a) {
-  __shared__ RecLds sm;
+struct RecLds {  // dynamic: the copies of the length sums and histograms follow
+  unsigned long long tok[kRecSlots];
+  uint32_t key[kRecSlots], req[kRecSlots];
+  unsigned long long red[kRecThreads / 64];
+};
+__host__ __device__ inline int rec_copies(int32_t A) { return A * 2 <= kRecApps ? 2 : 1; }
+inline size_t rec_lds_bytes(int32_t A) {
+  return sizeof(RecLds) + size_t(rec_copies(A)) * (size_t(A) * 3 * 8 + size_t(A) * 3 * kLenBins * 4 + 8);
+}
+
+__global__ void __launch_bounds__(kRecThreads) k_ws_records_hash(WsArgs a) {
+  extern __shared__ __align__(16) unsigned char w_smem[];
+  RecLds &sm = *reinterpret_cast<RecLds *>(w_smem);
   const DevTrace &t = a.t;
-  int32_t code = 0;
-  unsigned long long *const lh = reinterpret_cast<unsigned long long *>(a.o.len_hist);
-  unsigned long long *const lsum = reinterpret_cast<unsigned long long *>(a.o.len_sum);
-  const int64_t c0 = blockIdx.x * int64_t(kChunk);
-  const int64_t c1 = c0 + kChunk < t.N ? c0 + kChunk : t.N;
-  const int32_t A = t.A;
+  const int32_t A = t.A, nls = A * 3, nlh = A * 3 * kLenBins, copies = rec_copies(A);
+  unsigned long long *const ls = reinterpret_cast<unsigned long long *>(w_smem + sizeof(RecLds));
+  uint32_t *const lh = reinterpret_cast<uint32_t *>(ls + copies * nls);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (LDS) {
-    for (int k = threadIdx.x; k < A * 3 * kLenBins; k += kThreads) sm.lh[k] = 0;
-    for (int k = threadIdx.x; k < A * 3; k += kThreads) sm.ls[k] = 0;
+  const int cp = lane & (copies - 1);
+  unsigned long long *const ls_c = ls + cp * nls;
+  uint32_t *const lh_c = lh + cp * (nlh + 1);
+  int32_t code = 0;
+  for (int k = threadIdx.x; k < kRecSlots; k += kRecThreads) {
+    sm.tok[k] = 0;
+    sm.key[k] = kRecEmpty;
+    sm.req[k] = 0;
   }
+  for (int k = threadIdx.x; k < copies * nls; k += kRecThreads) ls[k] = 0;
+  for (int k = threadIdx.x; k < copies * (nlh + 1); k += kRecThreads) lh[k] = 0;
+  const int64_t c0 = blockIdx.x * int64_t(a.chunk);
+  const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
   int32_t r = c0 < c1 ? replica_of(t.rep_off, t.R, c0) : 0;
   for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
     while (t.rep_off[r + 1] <= s0) ++r;  // (empty replicas)
     const int64_t base = t.rep_off[r];
     const int64_t s1 = t.rep_off[r + 1] < c1 ? t.rep_off[r + 1] : c1;
     __syncthreads();
+    unsigned long long mts = 0;
+    bool any = false;
+    for (int64_t g0 = s0 + threadIdx.x; g0 < s1; g0 += 2 * kRecThreads) {  // loads of two together
+      int32_t u[2], ap[2], hd[2], L[2][3];
+      int64_t ts[2];
+      bool first[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int64_t g = g0 + j * kRecThreads;
+        const bool v = g < s1;
+        u[j] = v ? t.user[g] : 0;
+        ap[j] = v ? t.app[g] : 0;
+        ts[j] = v ? t.ts[g] : 0;
+        L[j][0] = v ? t.len_in[g] : 0;
+        L[j][1] = (v && t.len_sys) ? t.len_sys[g] : 0;
+        L[j][2] = v ? t.len_out[g] : 0;
+        first[j] = !(v && t.call && t.call[g] != 0);
+        hd[j] = (v && t.call) ? t.head[g] : 0;
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int64_t g = g0 + j * kRecThreads, i = g - base;
+        if (g >= s1) continue;
+        bool ok = u[j] >= 0 && u[j] < t.U && ap[j] >= 0 && ap[j] < A && ts[j] >= 0 &&
+                  len_ok(L[j][0]) && len_ok(L[j][1]) && len_ok(L[j][2]);
+        if (ok && !first[j]) ok = hd[j] >= 0 && hd[j] < i;
+        if (!ok) {
+          code = FS_E_RANGE;
+          continue;
+        }
+        mts = (unsigned long long)ts[j] > mts ? (unsigned long long)ts[j] : mts;
+        any = true;
+        const unsigned long long tok =
+            (unsigned long long)(int64_t(L[j][0]) + int64_t(L[j][1]) + int64_t(L[j][2]));
+        const uint32_t key = uint32_t((int64_t(r) * t.U + u[j]) * A + ap[j]);
+        uint32_t s = (key * 2654435761u) >> (32 - kRecBits);
+        int p = 0;
+        for (; p < kRecProbes; ++p, s = (s + 1) & (kRecSlots - 1)) {
+          uint32_t k = sm.key[s];
+          if (k == kRecEmpty) k = atomicCAS(&sm.key[s], kRecEmpty, key);
+          if (k == kRecEmpty || k == key) break;
+        }
+        if (p < kRecProbes) {
+          atomicAdd(&sm.req[s], 1u);
+          if (tok) atomicAdd(&sm.tok[s], tok);
+        } else {  // (the table is full around the slot)
+          atomicAdd(a.ua_req + key, 1ull);
+          if (tok) atomicAdd(a.ua_tok + key, tok);
+        }
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+          atomicAdd(&lh_c[(ap[j] * 3 + x) * kLenBins + len_bin(L[j][x])], 1u);
+          if (L[j][x]) atomicAdd(&ls_c[ap[j] * 3 + x], (unsigned long long)L[j][x]);
+        }
+        if (!first[j]) atomicAdd(a.size + base + hd[j], 1u);
+      }
+    }
+    // the segment's latest arrival, once per work-group
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+      const unsigned long long o = (unsigned long long)__shfl_xor((long long)mts, m, 64);
+      mts = o > mts ? o : mts;
+    }
+    const bool any_w = __ballot(any) != 0;
+    if (lane == 0) sm.red[wave] = any_w ? mts + 1 : 0;  // 0: no valid request
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      unsigned long long m = 0;
+      for (int w = 0; w < kRecThreads / 64; ++w) m = sm.red[w] > m ? sm.red[w] : m;
+      if (m) atomicMax(a.max_ts + r, m - 1);
+    }
+    unsigned long long *const glh = reinterpret_cast<unsigned long long *>(a.o.len_hist) + int64_t(r) * nlh;
+    unsigned long long *const gls = reinterpret_cast<unsigned long long *>(a.o.len_sum) + int64_t(r) * nls;
+    for (int k = threadIdx.x; k < nlh; k += kRecThreads) {
+      uint32_t c = 0;
+      for (int q = 0; q < copies; ++q) {
+        c += lh[q * (nlh + 1) + k];
+        lh[q * (nlh + 1) + k] = 0;
+      }
+      if (c) atomicAdd(glh + k, (unsigned long long)c);
+    }
+    for (int k = threadIdx.x; k < nls; k += kRecThreads) {
+      unsigned long long c = 0;
+      for (int q = 0; q < copies; ++q) {
+        c += ls[q * nls + k];
+        ls[q * nls + k] = 0;
+      }
+      if (c) atomicAdd(gls + k, c);
+    }
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < kRecSlots; k += kRecThreads) {
+    const uint32_t key = sm.key[k];
+    if (key == kRecEmpty) continue;
+    atomicAdd(a.ua_req + key, (unsigned long long)sm.req[k]);
+    if (sm.tok[k]) atomicAdd(a.ua_tok + key, sm.tok[k]);
+  }
+  if (code) raise_err(a.err, code);
+}
+
+// The records pass for more applications than an LDS table takes, or more (replica, user,
+// app) keys than 32 bits: aggregated per wave.
+__global__ void __launch_bounds__(kThreads) k_ws_records(WsArgs a) {
+  const DevTrace &t = a.t;
+  int32_t code = 0;
+  unsigned long long *const lh = reinterpret_cast<unsigned long long *>(a.o.len_hist);
+  unsigned long long *const lsum = reinterpret_cast<unsigned long long *>(a.o.len_sum);
+  const int64_t c0 = blockIdx.x * int64_t(a.chunk);
+  const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
+  const int32_t A = t.A;
+  const int lane = threadIdx.x & 63;
+  int32_t r = c0 < c1 ? replica_of(t.rep_off, t.R, c0) : 0;
+  for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
+    while (t.rep_off[r + 1] <= s0) ++r;  // (empty replicas)
+    const int64_t base = t.rep_off[r];
+    const int64_t s1 = t.rep_off[r + 1] < c1 ? t.rep_off[r + 1] : c1;
     unsigned long long mts = 0;
     bool any = false;
     // whole waves step through the segment so that every lane joins the reductions
@@ -171,56 +318,30 @@ __global__ void __launch_bounds__(kThreads) k_ws_records(WsArgs a) {
                       a.ua_req, a.ua_tok);
 #pragma unroll
       for (int x = 0; x < 3; ++x) {
-        if (LDS) {
-          if (ok) {
-            atomicAdd(&sm.lh[(ap * 3 + x) * kLenBins + len_bin(L[x])], 1u);
-            if (L[x]) atomicAdd(&sm.ls[ap * 3 + x], (unsigned long long)L[x]);
-          }
-        } else {
-          const int64_t ra = (int64_t(r) * A + ap) * 3 + x;
-          wave_add2<true>(ok, ra * kLenBins + len_bin(L[x]), 1ull, 0ull, lh, nullptr);
-          wave_add2<false>(ok && L[x] != 0, ra, (unsigned long long)L[x], 0ull, lsum, nullptr);
-        }
+        const int64_t ra = (int64_t(r) * A + ap) * 3 + x;
+        wave_add2<true>(ok, ra * kLenBins + len_bin(L[x]), 1ull, 0ull, lh, nullptr);
+        wave_add2<false>(ok && L[x] != 0, ra, (unsigned long long)L[x], 0ull, lsum, nullptr);
       }
       if (ok && h != g - base) atomicAdd(a.size + base + h, 1u);
     }
-    // the segment's latest arrival, once per work-group
+    // the segment's latest arrival, once per wave
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) {
       const unsigned long long o = (unsigned long long)__shfl_xor((long long)mts, m, 64);
       mts = o > mts ? o : mts;
     }
     const bool any_w = __ballot(any) != 0;
-    if (lane == 0) sm.red[wave] = any_w ? mts + 1 : 0;  // 0: no valid request
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      unsigned long long m = 0;
-      for (int w = 0; w < kThreads / 64; ++w) m = sm.red[w] > m ? sm.red[w] : m;
-      if (m) atomicMax(a.max_ts + r, m - 1);
-    }
-    if (LDS) {
-      for (int k = threadIdx.x; k < A * 3 * kLenBins; k += kThreads) {
-        const uint32_t c = sm.lh[k];
-        if (c) {
-          atomicAdd(lh + int64_t(r) * A * 3 * kLenBins + k, (unsigned long long)c);
-          sm.lh[k] = 0;
-        }
-      }
-      for (int k = threadIdx.x; k < A * 3; k += kThreads) {
-        const unsigned long long c = sm.ls[k];
-        if (c) {
-          atomicAdd(lsum + int64_t(r) * A * 3 + k, c);
-          sm.ls[k] = 0;
-        }
-      }
-    }
+    if (lane == 0 && any_w) atomicMax(a.max_ts + r, mts);
   }
   if (code) raise_err(a.err, code);
 }
 
+constexpr int kGraphCopies = 32;
 struct GraphLds {
   uint32_t sh[kLdsApps * kSizeBins];        // size histogram [A][bins]
-  unsigned long long gr[kGraphBins * 5];    // Table 2 rows
+  // Table 2 rows, a copy a lane pair: most requests are of one row, so with one copy every
+  // lane of a wave added to the same words (163 us over 10M requests)
+  unsigned long long gr[kGraphBins * 5 * kGraphCopies];
 };
 
 template <bool LDS>
@@ -229,10 +350,10 @@ __global__ void __launch_bounds__(kThreads) k_ws_graph(WsArgs a) {
   const DevTrace &t = a.t;
   unsigned long long *const gr = reinterpret_cast<unsigned long long *>(a.o.graph);
   unsigned long long *const sh = reinterpret_cast<unsigned long long *>(a.o.size_hist);
-  const int64_t c0 = blockIdx.x * int64_t(kChunk);
-  const int64_t c1 = c0 + kChunk < t.N ? c0 + kChunk : t.N;
+  const int64_t c0 = blockIdx.x * int64_t(a.chunk);
+  const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
   const int32_t A = t.A;
-  for (int k = threadIdx.x; k < kGraphBins * 5; k += kThreads) sm.gr[k] = 0;
+  for (int k = threadIdx.x; k < kGraphBins * 5 * kGraphCopies; k += kThreads) sm.gr[k] = 0;
   if (LDS)
     for (int k = threadIdx.x; k < A * kSizeBins; k += kThreads) sm.sh[k] = 0;
   int32_t r = c0 < c1 ? replica_of(t.rep_off, t.R, c0) : 0;
@@ -251,13 +372,13 @@ __global__ void __launch_bounds__(kThreads) k_ws_graph(WsArgs a) {
       if (!ok) continue;
       const uint32_t sz = a.size[base + h];
       const int b = graph_bin(sz);
-      unsigned long long *row = sm.gr + b * 5;
+      unsigned long long *row = sm.gr + b * 5 * kGraphCopies + (threadIdx.x & (kGraphCopies - 1));
       if (first) atomicAdd(row, 1ull);
-      atomicAdd(row + 1, 1ull);
+      atomicAdd(row + kGraphCopies, 1ull);
       const int64_t li = t.len_in[g], lo = t.len_out[g], ls = t.len_sys ? t.len_sys[g] : 0;
-      if (li) atomicAdd(row + 2, (unsigned long long)li);
-      if (lo) atomicAdd(row + 3, (unsigned long long)lo);
-      if (ls) atomicAdd(row + 4, (unsigned long long)ls);
+      if (li) atomicAdd(row + 2 * kGraphCopies, (unsigned long long)li);
+      if (lo) atomicAdd(row + 3 * kGraphCopies, (unsigned long long)lo);
+      if (ls) atomicAdd(row + 4 * kGraphCopies, (unsigned long long)ls);
       if (first && sz > 0) {
         const int sb = (sz < kSizeBins ? int(sz) : kSizeBins) - 1;
         if (LDS)
@@ -268,11 +389,12 @@ __global__ void __launch_bounds__(kThreads) k_ws_graph(WsArgs a) {
     }
     __syncthreads();
     for (int k = threadIdx.x; k < kGraphBins * 5; k += kThreads) {
-      const unsigned long long c = sm.gr[k];
-      if (c) {
-        atomicAdd(gr + int64_t(r) * kGraphBins * 5 + k, c);
-        sm.gr[k] = 0;
+      unsigned long long c = 0;
+      for (int q = 0; q < kGraphCopies; ++q) {
+        c += sm.gr[k * kGraphCopies + q];
+        sm.gr[k * kGraphCopies + q] = 0;
       }
+      if (c) atomicAdd(gr + int64_t(r) * kGraphBins * 5 + k, c);
     }
     if (LDS)
       for (int k = threadIdx.x; k < A * kSizeBins; k += kThreads) {
@@ -326,6 +448,57 @@ __global__ void __launch_bounds__(kThreads) k_ws_users(WsArgs a, int64_t RU) {
     wave_add2<true>(n > 0, row * kRateBins + rate_bin(n, M), 1ull, 0ull, rh, nullptr);
     wave_add2<true>(n > 0, (row + 1) * kRateBins + rate_bin(tk, M), 1ull, 0ull, rh, nullptr);
   }
+}
+
+// The same with the rate histograms of a replica's kUserSpan users in LDS (apps up to
+// kRateApps): the entries of the users' rows read in order, one count a user or entry.
+constexpr int kUserSpan = 256;
+constexpr int kRateApps = 64;
+inline size_t users_lds_bytes(int32_t A) { return size_t(A + 1) * 2 * kRateBins * 4; }
+
+constexpr int kUserThreads = 512;
+__global__ void __launch_bounds__(kUserThreads) k_ws_users_lds(WsArgs a) {
+  extern __shared__ uint32_t s_rate[];  // [A + 1][2][kRateBins]
+  const DevTrace &t = a.t;
+  const int32_t A = t.A;
+  const int32_t per = (t.U + kUserSpan - 1) / kUserSpan;
+  const int32_t r = int32_t(blockIdx.x / per), u0 = int32_t(blockIdx.x % per) * kUserSpan;
+  const int32_t nu = t.U - u0 < kUserSpan ? t.U - u0 : kUserSpan;
+  const int n_rate = (A + 1) * 2 * kRateBins;
+  const bool has = t.rep_off[r + 1] > t.rep_off[r];
+  const uint64_t M = has ? a.max_ts[r] / uint64_t(a.minute_us) + 1 : 0;
+  const uint64_t Md = M ? M : 1;
+  for (int k = threadIdx.x; k < n_rate; k += kUserThreads) s_rate[k] = 0;
+  __syncthreads();
+  const int64_t ru0 = int64_t(r) * t.U + u0;
+  for (int64_t k = threadIdx.x; k < int64_t(nu) * A; k += kUserThreads) {
+    const unsigned long long n = a.ua_req[ru0 * A + k];
+    if (n > 0) {
+      const unsigned long long tk = a.ua_tok[ru0 * A + k];
+      const int ap = int(uint32_t(k) % uint32_t(A));
+      atomicAdd(&s_rate[ap * 2 * kRateBins + rate_bin(n, Md)], 1u);
+      atomicAdd(&s_rate[(ap * 2 + 1) * kRateBins + rate_bin(tk, Md)], 1u);
+    }
+  }
+  for (int32_t u = threadIdx.x; u < nu; u += kUserThreads) {
+    const unsigned long long *const q = a.ua_req + (ru0 + u) * A, *const w = a.ua_tok + (ru0 + u) * A;
+    unsigned long long nq = 0, nt = 0;
+    for (int32_t ap = 0; ap < A; ++ap) {
+      nq += q[ap];
+      nt += w[ap];
+    }
+    a.o.user_req[ru0 + u] = int64_t(nq);
+    a.o.user_tok[ru0 + u] = int64_t(nt);
+    if (nq > 0) {
+      atomicAdd(&s_rate[A * 2 * kRateBins + rate_bin(nq, Md)], 1u);
+      atomicAdd(&s_rate[(A * 2 + 1) * kRateBins + rate_bin(nt, Md)], 1u);
+    }
+  }
+  if (u0 == 0 && threadIdx.x == 0) a.o.minutes[r] = int64_t(M);
+  __syncthreads();
+  unsigned long long *const rh = reinterpret_cast<unsigned long long *>(a.o.rate_hist) + int64_t(r) * n_rate;
+  for (int k = threadIdx.x; k < n_rate; k += kUserThreads)
+    if (s_rate[k]) atomicAdd(rh + k, (unsigned long long)s_rate[k]);
 }
 
 // One work-group per replica when the replica's (user, app) table fits in LDS (and
@@ -631,14 +804,38 @@ hipError_t launch_workload(const fs_trace *t, int64_t minute_us, const fs_wstats
                                          int64_t(t->n_replicas) * (t->n_apps + 1) * 2 * kRateBins);
   hipLaunchKernelGGL(k_ws_zero, dim3(grid_for(most)), dim3(kThreads), 0, s, a, RUA, RU);
   if (N > 0) {
-    const dim3 chunks(uint32_t((N + kChunk - 1) / kChunk));
-    if (t->n_apps <= kLdsApps) {
-      hipLaunchKernelGGL(k_ws_records<true>, chunks, dim3(kThreads), 0, s, a);
-      hipLaunchKernelGGL(k_ws_graph<true>, chunks, dim3(kThreads), 0, s, a);
+    // four chunks a CU where there are records enough
+    a.chunk = int32_t(std::min<int64_t>(kChunk, std::max<int64_t>(kChunkLeast, (N / 1024 + 255) / 256 * 256)));
+    const dim3 chunks(uint32_t((N + a.chunk - 1) / a.chunk));
+    if (t->n_apps <= kRecApps && RUA < int64_t(kRecEmpty)) {
+      const int32_t chunk = a.chunk;
+      // a whole number of work-groups a CU, each of at most kRecChunk records
+      const int64_t rounds = (N + int64_t(kRecChunk) * 256 - 1) / (int64_t(kRecChunk) * 256);
+      const int64_t per = (N + rounds * 256 - 1) / (rounds * 256);
+      a.chunk = int32_t(std::max<int64_t>((per + 255) / 256 * 256, 2048));
+      const size_t lds = rec_lds_bytes(t->n_apps);
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_ws_records_hash),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k_ws_records_hash, dim3(uint32_t((N + a.chunk - 1) / a.chunk)),
+                         dim3(kRecThreads), lds, s, a);
+      a.chunk = chunk;
     } else {
-      hipLaunchKernelGGL(k_ws_records<false>, chunks, dim3(kThreads), 0, s, a);
-      hipLaunchKernelGGL(k_ws_graph<false>, chunks, dim3(kThreads), 0, s, a);
+      hipLaunchKernelGGL(k_ws_records, chunks, dim3(kThreads), 0, s, a);
     }
+    if (t->n_apps <= kLdsApps)
+      hipLaunchKernelGGL(k_ws_graph<true>, chunks, dim3(kThreads), 0, s, a);
+    else
+      hipLaunchKernelGGL(k_ws_graph<false>, chunks, dim3(kThreads), 0, s, a);
+  }
+  const int64_t spans = int64_t(t->n_replicas) * ((t->n_users + kUserSpan - 1) / kUserSpan);
+  if (t->n_apps <= kRateApps && spans <= (int64_t(1) << 30)) {
+    const size_t lds = users_lds_bytes(t->n_apps);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_ws_users_lds),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_ws_users_lds, dim3(uint32_t(spans)), dim3(kUserThreads), lds, s, a);
+    return hipGetLastError();
   }
   hipLaunchKernelGGL(k_ws_users, dim3(grid_for(RUA > RU ? RUA : RU)), dim3(kThreads), 0, s, a, RU);
   return hipGetLastError();
