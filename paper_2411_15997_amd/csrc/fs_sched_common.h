@@ -109,7 +109,6 @@ struct OnchipCfg {
   int32_t inl_glds;   // the same two, for the global-memory pass that an on-chip
   int32_t inl_hblk;   // instance continues with, within its own LDS allocation
   int32_t p_cache;    // pool pass: recent arrivals kept on chip (power of two; 0: not run)
-  int32_t p_links;    // pool pass: entries of the spill lists' links (power of two)
   int32_t p_users;    // pool pass: 1 = counters of idle users in LDS
   int32_t p_tab;      // pool pass: entries (power of two) of the window's user table
   size_t lds_bytes;

@@ -181,7 +181,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       const Ent e = valid ? bat[i] : mk_ent(-1, int32_t(kDeadFin), 0, 0);
       const int32_t ku = valid ? bat_u[i] : -1;
       const bool live = valid && uint32_t(e.succ) != kDeadFin;
-      const uint64_t km = __ballot(live);
+      const uint64_t km = bal(live);
       if (live) {
         const int32_t to = kept + __popcll(km & lt);
         bat[to] = e;
@@ -247,7 +247,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     const bool sat = oc && (d < 0 || d >= int64_t(kRelMax));
     const uint32_t rv = sat ? kRelMax : uint32_t(d);
     k32 = oc ? (((kh & kTier1) << 1) | rv) : 0xffffffffu;
-    wide = __ballot(sat) != 0;
+    wide = bal(sat) != 0;
   };
 
   // First call (rec, sc, lo, hi) joins the tail of slot x's FIFO: on chip while the
@@ -339,7 +339,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       xsb = sb;
       xn = 0;
     }
-    const uint64_t km = __ballot(w_user == k);
+    const uint64_t km = bal(w_user == k);
     w_slot = (w_user == k) ? x : w_slot;
     xwm = lane == x ? km : xwm;
     return x;
@@ -404,7 +404,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
   // who lost its entry sends the window to the matching bit by bit.
   auto match_window = [&]() {
     const bool wv = w_user >= 0;
-    const uint64_t wvm = __ballot(wv);
+    const uint64_t wvm = bal(wv);
     const int32_t hw = w_user & (u_tab - 1), hx = xu & (u_tab - 1);
     if (wv) u_rep[hw] = uint8_t(lane);
     if (xu >= 0) u_slot[hx] = uint8_t(lane);
@@ -419,10 +419,10 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     const int32_t rp = (wv && rr < 64 && rr_user == w_user) ? rr : 64;
     const int32_t rxv = (xu >= 0 && rx < 64 && rx_user == xu) ? rx : 64;
     uint64_t g = wvm, m = wvm;
-    if (!__ballot(lost || (wv && rp == 64))) {
+    if (!bal(lost || (wv && rp == 64))) {
       w_slot = (wv && xs < 64 && ((occ >> xs) & 1) && xs_user == w_user) ? xs : -1;
       for (int b = 0; b < 6; ++b) {  // lanes match on their representative's bits
-        const uint64_t W = __ballot(wv && ((rp >> b) & 1));
+        const uint64_t W = bal(wv && ((rp >> b) & 1));
         g &= ((rp >> b) & 1) ? W : ~W;
         m &= ((rxv >> b) & 1) ? W : ~W;
       }
@@ -431,7 +431,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       uint64_t sm = occ;
       for (int b = 0; b < ubits; ++b) {
         const bool wb = (uint32_t(w_user) >> b) & 1u, xb = (uint32_t(xu) >> b) & 1u;
-        const uint64_t W = __ballot(wv && wb), S = __ballot(xu >= 0 && xb);
+        const uint64_t W = bal(wv && wb), S = bal(xu >= 0 && xb);
         g &= wb ? W : ~W;
         sm &= wb ? S : ~S;
         m &= xb ? W : ~W;
@@ -543,7 +543,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     fetch(pf_at + lane, pf);
     const int32_t lo_ = wbase + 64 - M;
     cache_lo = lo_ > cache_from ? lo_ : cache_from;
-    w_wait = LINKS && __ballot(w_user >= 0 && !(w_flags & (kFirst | kPrevAdm))) != 0;
+    w_wait = LINKS && bal(w_user >= 0 && !(w_flags & (kFirst | kPrevAdm))) != 0;
     match_window();
   };
   auto advance_window = [&]() {
@@ -566,7 +566,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     const int32_t why = (w_flags >> kReasonShift) & 3;
     const uint32_t tok = w_lo & uint32_t(kTokMask);
     bool bf = false;  // a first call throttled (over a limit while the system is overloaded)
-    if (__ballot(inb && first && why != 0)) {
+    if (bal(inb && first && why != 0)) {
       const uint32_t c0 = (inb && (first || !(w_flags & kHeadBlk))) ? tok : 0u;
       const uint32_t excl = wave_incl_scan32(c0) - c0;
       const int64_t thr = theta - backlog;  // overloaded at a lane iff excl > thr
@@ -576,7 +576,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     }
     // a later call shares its first call's fate: throttled before the batch or in it
     bool hb_new = false;
-    if (__ballot(bf)) {
+    if (bal(bf)) {
       const int32_t hl = w_head - wbase;
       const bool hl_in = hl >= j0 && hl < j1;
       const int hb_src = __builtin_amdgcn_ds_bpermute((hl_in ? hl : lane) << 2, bf ? 1 : 0);
@@ -584,10 +584,10 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     }
     const bool bl = inb && !first && ((w_flags & kHeadBlk) || hb_new);
     const bool blk = bf || bl;
-    const uint64_t ub = __ballot(inb && !blk);
+    const uint64_t ub = bal(inb && !blk);
     const uint64_t rdym =
-        (fcfs || !LINKS) ? 0 : __ballot(inb && !blk && !first && (w_flags & kPrevAdm));
-    if (__ballot(inb && !blk && (w_flags & kBig)) || __popcll(ub) > kSlots - nX ||
+        (fcfs || !LINKS) ? 0 : bal(inb && !blk && !first && (w_flags & kPrevAdm));
+    if (bal(inb && !blk && (w_flags & kBig)) || __popcll(ub) > kSlots - nX ||
         __popcll(rdym) > kSlots - __popcll(pocc))
       return false;
     w_flags |= hb_new ? kHeadBlk : 0;
@@ -596,12 +596,12 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     // same: batch lanes with this lane's user; x0: the slot holding this lane's user;
     // mx: batch lanes with this slot's user
     const uint64_t lt = (uint64_t(1) << lane) - 1;
-    const uint64_t inbm = __ballot(inb);
+    const uint64_t inbm = bal(inb);
     const uint64_t same = w_gm & inbm;
     uint64_t mx = xwm & inbm;
     const int32_t x0 = w_slot;
     const int32_t lead = ff1(same);  // the user's first lane in the batch
-    const uint64_t newm = __ballot(inb && x0 < 0);
+    const uint64_t newm = bal(inb && x0 < 0);
     // users outside Q are lifted to the least counter in Q, on every arrival
     const int64_t lifted = c_u > minX ? c_u : minX;
     const bool is_lead = inb && lane == lead;
@@ -620,7 +620,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     // result (ties go by user id), so each takes the slot of its own lane when all of
     // those are free, else the i-th takes the i-th free slot.
     const bool jl = is_lead && x0 < 0 && (same & ub) != 0;
-    const uint64_t jm = __ballot(jl);
+    const uint64_t jm = bal(jl);
     int32_t xj = x0;
     if (jm && !(jm & occ)) {
       bool sat = false;
@@ -638,7 +638,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
         mx = same;
         xwm = w_gm;
       }
-      if (__ballot(sat)) wide = true;
+      if (bal(sat)) wide = true;
       occ |= jm;
       nX += __popcll(jm);
       // every window lane of a joining user: the slot is its first batch lane
@@ -682,8 +682,8 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
         xwm = (uint64_t(e.mhi) << 32) | e.mlo;
         mx = xwm & inbm;
       }
-      if (__ballot(sat)) wide = true;
-      occ |= __ballot(ns);
+      if (bal(sat)) wide = true;
+      occ |= bal(ns);
       nX += J;
       // every window lane of a joining user takes its slot from its first batch lane
       const int32_t xl = __builtin_amdgcn_ds_bpermute((lead >= 0 ? lead : lane) << 2, xj);
@@ -693,7 +693,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       }
     }
     // per slot: queued calls, first calls for its FIFO (in lane order), ready calls
-    const uint64_t F = ub & (fcfs ? ~uint64_t(0) : __ballot(first));
+    const uint64_t F = ub & (fcfs ? ~uint64_t(0) : bal(first));
     const bool oc = xu >= 0;
     const uint64_t mF = oc ? (mx & F) : 0, mR = oc ? (mx & rdym) : 0, mU = oc ? (mx & ub) : 0;
     const int32_t cF = __popcll(mF), cR = __popcll(mR), cU = __popcll(mU);
@@ -768,7 +768,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
         p_lo = e.lo;
         p_hi = e.hi;
       }
-      pocc |= __ballot(np);
+      pocc |= bal(np);
       if (cR > 0) {
         xn += cR;
         kh &= kValHi;  // tier 0
@@ -783,7 +783,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     const int8_t *const fate = STATE(const int8_t, fate) + base;
     const int32_t i = b0 + lane;
     const bool q = i < nxt && ld_fresh(fate + i) == -1;
-    uint64_t m = __ballot(q);
+    uint64_t m = bal(q);
     while (m && !overflow) {
       const int l = ff1(m);
       m &= m - 1;
@@ -796,7 +796,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       uint32_t lo, hi;
       load_rec(rec, sc, lo, hi);
       const bool padm = !fcfs && call > 0 && ld_fresh(fate + uni(KARG(t.prev)[g])) == 0;
-      const uint64_t fm = __ballot(xu == k);
+      const uint64_t fm = bal(xu == k);
       const bool big = KARG(cost)[g] >= kPackLimit;
       if (big || (fm == 0 && nX == kSlots) || (padm && pocc == ~uint64_t(0))) {
         overflow = true;  // nothing in the state buffer has changed yet
@@ -877,20 +877,20 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     const uint64_t nkey = W ? (uint64_t(unew) | (uint64_t(kTier1) << 32))
                             : ((uint64_t(nk) << 32) | uint32_t(xu));
     uint32_t cut = uint32_t(64 - nd);  // room left in the output staging
-    for (uint64_t sm = __ballot(stay); sm; sm &= sm - 1) {
+    for (uint64_t sm = bal(stay); sm; sm &= sm - 1) {
       const int32_t j = ff1(sm);
       uint32_t cj = rdlu(rank, j) + 1;  // (a saturated return: stop after it, full keys follow)
       if (W || !rdlu(uint32_t(nsat), j)) {
         const uint64_t nkj = (uint64_t(rdlu(uint32_t(nkey >> 32), j)) << 32) | rdlu(uint32_t(nkey), j);
         const uint32_t uj = W ? rdlu(kuser, j) : 0u;
-        const uint32_t cnt = uint32_t(__popcll(__ballot(oc && before(key, kuser, nkj, uj))));
+        const uint32_t cnt = uint32_t(__popcll(bal(oc && before(key, kuser, nkj, uj))));
         cj = cnt > cj ? cnt : cj;
       }
       cut = cj < cut ? cj : cut;
     }
     const bool fin = adm && rank < cut;
-    const uint64_t fm = __ballot(fin);
-    if (!fm || __ballot(fin && unew >= kValueLimit)) return 0;
+    const uint64_t fm = bal(fin);
+    if (!fm || bal(fin && unew >= kValueLimit)) return 0;
     const int32_t m = __popcll(fm);  // the admitted hold ranks 0 .. m - 1
     // outputs, in admission order, into staging lanes nd .. nd + m - 1: the admitted lane
     // of rank q sends to lane nd + q, the i-th other lane to the i-th lane outside the
@@ -906,7 +906,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       d_step = s;
       d_cnt = int64_t((uint64_t(o_hi) << 32) | o_lo);
     }
-    const int32_t lastl = ff1(__ballot(fin && rank == uint32_t(m - 1)));  // the last admitted
+    const int32_t lastl = ff1(bal(fin && rank == uint32_t(m - 1)));  // the last admitted
     const uint32_t used = rdlu(pre + tok, lastl);
     budget -= int64_t(used);
     backlog -= int64_t(used);
@@ -915,11 +915,11 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     // users that leave Q: the last one in admission order is e; counters back to u;
     // window lanes of those users (w_slot is the slot of a lane's user) take the counter
     const bool lv = fin && xq == 1;
-    const uint64_t lm = __ballot(lv);
+    const uint64_t lm = bal(lv);
     if (lm) {
       uint32_t q = uint32_t(m - 1);
       int32_t ll = lastl;
-      while (!((lm >> ll) & 1)) ll = ff1(__ballot(fin && rank == --q));
+      while (!((lm >> ll) & 1)) ll = ff1(bal(fin && rank == --q));
       last_exit = rdl(xu, ll);
       last_exit_u = rdl64(unew, ll);
       if (lv) set_u(xu, unew);
@@ -940,7 +940,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       ++xf;
       --xq;
     }
-    for (uint64_t rm = __ballot(stay && fin && xf == xr && xr < xt); rm; rm &= rm - 1)
+    for (uint64_t rm = bal(stay && fin && xf == xr && xr < xt); rm; rm &= rm - 1)
       fifo_refill(ff1(rm));
     if (stay && fin) {
       if (xf < xt) {
@@ -954,7 +954,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       kl = uint32_t(uint64_t(unew));
       k32 = nk;
     }
-    if (__ballot(stay && fin && nsat)) wide = true;
+    if (bal(stay && fin && nsat)) wide = true;
     if (lv) {
       kh = kl = k32 = 0xffffffffu;
       xu = -1;
@@ -1017,7 +1017,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     } else {
       // the next head (refilled from the segment first when the on-chip part is used
       // up) and the key at the charged counter
-      if (FS_RARE((__ballot(xf == xr && xr < xt) >> x) & 1)) fifo_refill(x);
+      if (FS_RARE((bal(xf == xr && xr < xt) >> x) & 1)) fifo_refill(x);
       const uint32_t rv = rel_of(u);
       if (lane == x) {
         const Ent v = ring[x * D + (xf & (D - 1))];
@@ -1089,7 +1089,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       // (nothing is queued), joins lifted to the last exit's counter, and is then the
       // least counter in Q, so the others are lifted to it
       if (!blind && (nX > 0 || (!LINKS && theta >= 0))) {
-        const uint64_t after = __ballot(w_step > s) & (~uint64_t(0) << j);
+        const uint64_t after = bal(w_step > s) & (~uint64_t(0) << j);
         const int32_t j1 = after ? ff1(after) : 64;
         if (j1 - j > 1) {
           bool done;
@@ -1119,7 +1119,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       const int32_t rec = nxt;
       const int32_t k = rdl(w_user, j);
       const int32_t fl = rdl(w_flags, j);
-      const uint64_t fm = __ballot(xu == k);
+      const uint64_t fm = bal(xu == k);
       const int32_t xs = ff1(fm);
       int64_t uk, u_before = 0;
       if (fm) {
@@ -1194,7 +1194,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
         // first come, first served: the earliest of the FIFO heads (each user's FIFO
         // holds all of its queued calls in arrival order)
         const uint32_t hv = (xu >= 0 && xf < xt) ? uint32_t(hrec) : 0xffffffffu;
-        x = ff1(__ballot(hv == wave_min32v(hv)));
+        x = ff1(bal(hv == wave_min32v(hv)));
         tier0 = false;
         uk = int64_t((uint64_t(rdlu(kh, x) & kValHi) << 32) | rdlu(kl, x));
       } else {
@@ -1211,10 +1211,10 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
           tier0 = LINKS && mh < kTier1;
           uk = int64_t((uint64_t(mh & kValHi) << 32) | ml);
         }
-        const uint64_t eq = __ballot(cand);
+        const uint64_t eq = bal(cand);
         if (FS_RARE(eq & (eq - 1))) {
           const uint32_t um = wave_min32v(cand ? uint32_t(xu) : 0xffffffffu);
-          x = ff1(__ballot(cand && uint32_t(xu) == um));
+          x = ff1(bal(cand && uint32_t(xu) == um));
         } else {
           x = ff1(eq);
         }
@@ -1222,11 +1222,11 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       int32_t rec, sc;
       uint32_t lo, hi;
       if (tier0) {  // the user's earliest ready later call
-        const uint64_t pm = __ballot(p_x == x);
+        const uint64_t pm = bal(p_x == x);
         l = ff1(pm);
         if (FS_RARE(pm & (pm - 1))) {
           const uint32_t e = wave_min32v(p_x == x ? uint32_t(p_rec) : 0xffffffffu);
-          l = ff1(__ballot(p_x == x && uint32_t(p_rec) == e));
+          l = ff1(bal(p_x == x && uint32_t(p_rec) == e));
         }
         rec = rdl(p_rec, l);
         sc = rdl(p_succ, l);
@@ -1300,7 +1300,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       } else {
         if (lane == x) ++xf;
         // the on-chip part of the FIFO is used up and its segment holds more: refill
-        if (FS_RARE((__ballot(xf == xr && xr < xt) >> x) & 1)) fifo_refill(x);
+        if (FS_RARE((bal(xf == xr && xr < xt) >> x) & 1)) fifo_refill(x);
         if (lane == x && xf < xt) {
           const Ent v = ring[x * D + (xf & (D - 1))];
           hrec = v.rec;
@@ -1362,13 +1362,13 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       }
       for (int32_t c = nb0 >> 6; c * 64 < n_run; ++c) chunk_min(c);
       nb0 = n_run;
-      if (FS_RARE(__ballot(big) != 0)) code = FS_E_OVERFLOW;  // the step count would overflow
+      if (FS_RARE(bal(big) != 0)) code = FS_E_OVERFLOW;  // the step count would overflow
     }
     if (FS_RARE(overflow || code)) break;
     if (LITERAL) {
       // decode: calls whose last output token falls in step s finish in admission
       // order; each user is charged its call's cost and the call's KV is freed
-      uint64_t due = __ballot(cmin <= uint32_t(s));
+      uint64_t due = bal(cmin <= uint32_t(s));
       if (due) stalled = false;
       int64_t *const ca = KARG(counter_after);
       while (due && !code) {
@@ -1380,7 +1380,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
         const int32_t ku = valid ? bat_u[i] : -1;
         const bool done = valid && e.succ == s;
         if (done) bat[i].succ = int32_t(kDeadFin);
-        uint64_t dm = __ballot(done);
+        uint64_t dm = bal(done);
         n_live -= __popcll(dm);
         while (dm) {
           const int l = ff1(dm);
@@ -1388,7 +1388,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
           const int32_t rec = rdl(e.rec, l), k = rdl(ku, l);
           const uint32_t elo = rdlu(e.lo, l), ehi = rdlu(e.hi, l);
           const int64_t cst = int64_t(((uint64_t(ehi) << 32) | elo) >> 24);
-          const uint64_t fm = __ballot(xu == k);
+          const uint64_t fm = bal(xu == k);
           int64_t uc;
           if (fm) {  // a queued user: its key moves, its tier stays
             const int32_t xx = ff1(fm);
@@ -1480,7 +1480,7 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     while (low < nxt) {
       const int32_t i = low + lane;
       const bool q = i < nxt && ld_fresh(fate + i) == -1;
-      const uint64_t m = __ballot(q);
+      const uint64_t m = bal(q);
       if (m) {
         low += ff1(m);
         break;
@@ -1563,8 +1563,7 @@ __global__ void __launch_bounds__(64) k_schedule_onchip(SchedArgs a) {
 
 // The paper's policy: the pool pass, and the pass above for a replica while it has outgrown
 // the pool (taken back when users and ready calls are down to kPoolBack, half the lanes, and
-// after a number of steps that doubles each time: a change of passes rebuilds the queue, and
-// what outgrew the pool may be more than its users, as a user's calls spilled too far apart).
+// after a number of steps that doubles each time: a change of passes rebuilds the queue).
 template <bool LINKS>
 __global__ void __launch_bounds__(64) k_schedule_pool(SchedArgs a) {
   extern __shared__ __align__(16) char smem[];
@@ -1651,11 +1650,10 @@ OnchipCfg onchip_config(int32_t R, int32_t U, bool literal) {
 }
 
 // LDS of the pool pass, from the same budget per work-group: the counters of idle users
-// and the table that matches a window's users when they fit in a quarter each, the spill
-// links in up to two fifths of the rest (4,096 records on the weight sweep's 39 KB), and
-// the arrival cache.  User ids share a word with the position in the pool: 26 bits.
+// and the table that matches a window's users when they fit in a quarter each, and the
+// arrival cache.  User ids share a word with the position in the pool: 26 bits.
 void pool_config(int32_t R, int32_t U, OnchipCfg &c) {
-  c.p_cache = c.p_links = c.p_users = c.p_tab = 0;
+  c.p_cache = c.p_users = c.p_tab = 0;
   if (U > (1 << (32 - kAheadBits))) return;
   const int per_cu = R <= 256 ? 1 : R <= 512 ? 2 : R <= 768 ? 3 : 4;
   size_t budget = size_t(160 * 1024) / per_cu - 1024;
@@ -1667,13 +1665,10 @@ void pool_config(int32_t R, int32_t U, OnchipCfg &c) {
   while (tab < U && tab < 32768 && size_t(tab) * 2 <= budget / 4) tab <<= 1;
   c.p_tab = tab;
   const size_t left = budget - PoolLds::end - kStPad - users - size_t(tab);
-  int links = 16384;
-  while (links > 256 && size_t(links) * 2 > left * 2 / 5) links >>= 1;
-  c.p_links = links;
   int cache = 4096;
-  while (cache > 64 && size_t(cache) * (sizeof(Ent) + 1) > left - size_t(links) * 2) cache >>= 1;
+  while (cache > 64 && size_t(cache) * (sizeof(Ent) + 1) > left) cache >>= 1;
   c.p_cache = cache;
-  const size_t total = PoolLds::end + kStPad + size_t(cache) * (sizeof(Ent) + 1) + users + size_t(links) * 2 + size_t(tab);
+  const size_t total = PoolLds::end + kStPad + size_t(cache) * (sizeof(Ent) + 1) + users + size_t(tab);
   if (total > c.lds_bytes) c.lds_bytes = total;
 }
 

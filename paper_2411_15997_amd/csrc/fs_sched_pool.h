@@ -18,8 +18,8 @@
 //
 // Per-user state (a slot: the counter after the user's pooled calls, their number, the
 // spill list) and the counters of the window's users are in LDS, read and updated by the
-// lanes of the user's calls.  First calls beyond the pool's room go to a linked list over
-// record numbers in LDS; their data comes from the arrival cache, or the inputs.
+// lanes of the user's calls.  First calls beyond the pool's room go to the user's segment of
+// the state buffer and come back 16 at a time.
 //
 // One call per lane replaced one user per lane with sequential admissions (about 1,300
 // clocks each: an argmin, the chosen user's next call and its new key in a dependent
@@ -101,6 +101,8 @@ __device__ __forceinline__ int32_t step_of(int64_t ts, int64_t tau, double tau_i
 
 constexpr uint32_t kPTier1 = 0x80000000u;  // a first call, in the key's high word
 constexpr int kAheadBits = 6;              // position among the user's pooled calls
+// Calls the pool takes without looking at whose they are, and a user's share beyond that.
+constexpr int kPoolRoom = 28, kPoolShare = 6;
 constexpr int kNearMin = 20, kNearLeast = 8, kNearRank = 16;  // calls ranked of a large pool
 
 // A slot's record: the counter after the user's pooled calls; the number of pooled calls and
@@ -111,18 +113,21 @@ struct __align__(16) SlotRec {
 };
 constexpr uint32_t kNumMask = 0xffu, kRdyOne = 0x100u, kWinMask = 0xffu, kSpOne = 0x100u;
 
+constexpr int kOutStage = 192;  // admissions kept until the next window (then written together)
+
 // Byte offsets of the pool pass's LDS (the cache, counters, links and tables follow).
 // Entry 64 of an array takes the stores of lanes that have none to make.
 struct PoolLds {
   static constexpr int stage = 0;                // [65] two 16-byte words: calls placed
-  static constexpr int rank = stage + 65 * 32;   // [72] uint4, the rank's packed calls
-  static constexpr int slot = rank + 72 * 16;    // [65] SlotRec
+  static constexpr int adm = stage + 65 * 32;     // [kOutStage + 1] admitted records and steps
+  static constexpr int slot = adm + (kOutStage + 2) * 8;  // [65] SlotRec
   static constexpr int win = slot + 65 * 16;     // [65] a window user: counter (8), slot or -1 (4)
   static constexpr int uc = win + 65 * 16;       // [65] u64 the user's counter
   static constexpr int xu = uc + 66 * 8;         // [65] i32 user of the slot, -1 free
-  static constexpr int sph = xu + 66 * 4;        // [64] i32 first spilled record
-  static constexpr int spt = sph + 64 * 4;       // [64] i32 last spilled record
-  static constexpr int freex = spt + 64 * 4;     // [65] i32 free slots (a stack)
+  static constexpr int sph = xu + 66 * 4;        // [64] u32 first spilled call's place
+  static constexpr int seg = sph + 64 * 4;       // [64] u32 the user's segment
+  static constexpr int cap = seg + 64 * 4;       // [64] u32 its places
+  static constexpr int freex = cap + 64 * 4;     // [65] i32 free slots (a stack)
   static constexpr int end = (freex + 66 * 4 + 15) / 16 * 16;
 };
 // Entries of the request-state table past the cache's M: states of records it no longer holds.
@@ -130,24 +135,23 @@ constexpr int kStAdm = 0, kStNone = 1, kStBlk = 2, kStPad = 16;
 
 // Ranks of the pooled calls in the order of (key, user, position) and the tokens ranked
 // before each, as rank << 26 | tokens (the pool's tokens sum to less than 2^26).  p: the
-// order as one word.  The calls' words and tokens are packed in LDS and every lane reads
-// them one after the other (one 16-byte read of one address for all lanes, eight in flight,
-// then a compare, a select and an add: about 25 clocks a call against 42 with three lane
-// reads a call in place of the LDS read, and only the occupied lanes are visited).
-__device__ __forceinline__ uint32_t pool_rank(uint64_t p, uint32_t tok, uint64_t occ, uint4 *s_rank) {
-  const int32_t n = __popcll(occ);
-  if (in_mask(occ))
-    s_rank[below(occ)] = make_uint4(uint32_t(p), uint32_t(p >> 32), tok | (1u << 26), 0u);
-  s_rank[n + (threadIdx.x & 7)] = make_uint4(0xffffffffu, 0xffffffffu, 0u, 0u);
-  wave_fence();
+// order as one word, all ones in a lane without a ranked call.  The calls are lanes
+// [0, top) of sh, sl (their words) and sa (their tokens | 1 << 26), taken eight at a time
+// by lane reads: new calls take the lowest free lanes, so the pool's own lanes serve.
+// (Reading the words one after the other from LDS, one address for all lanes, took about
+// 95 clocks a call against 55: a 9-call ranking 1,080 clocks against 630.)
+__device__ __forceinline__ uint32_t pool_rank(uint64_t p, uint32_t sh, uint32_t sl, uint32_t sa, int32_t top) {
   uint32_t acc = 0;
-  for (int32_t j = 0; j < n; j += 8) {
-    uint4 e[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) e[i] = s_rank[j + i];
+  for (int b = 0; b < 8; ++b) {
+    if (8 * b >= top) break;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      acc += ((uint64_t(e[i].y) << 32) | e[i].x) < p ? e[i].z : 0u;
+    for (int i = 0; i < 8; ++i) {
+      const int j = 8 * b + i;
+      const uint64_t pj = (uint64_t(rdlu(sh, j)) << 32) | rdlu(sl, j);
+      const uint32_t aj = rdlu(sa, j);
+      acc += pj < p ? aj : 0u;
+    }
   }
   return acc;
 }
@@ -176,7 +180,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
   const int32_t r = blockIdx.x;
   const int lane = threadIdx.x;
   const uint64_t lt = (uint64_t(1) << lane) - 1;
-  const int32_t M = a.oc.p_cache, ML = a.oc.p_links, tab = a.oc.p_tab;
+  const int32_t M = a.oc.p_cache, tab = a.oc.p_tab;
   const bool ulds = a.oc.p_users != 0;
   const int32_t U = a.t.U;
   const int ubits = U > 1 ? 32 - __builtin_clz(uint32_t(U - 1)) : 0;
@@ -184,18 +188,18 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
   const bool want_coa = a.counter_on_arrival != nullptr;
   const bool want_seq = a.admit_seq != nullptr || a.counter_after != nullptr;
   uint4 *const s_stage = reinterpret_cast<uint4 *>(smem + PoolLds::stage);
-  uint4 *const s_rank = reinterpret_cast<uint4 *>(smem + PoolLds::rank);
+  uint2 *const s_adm = reinterpret_cast<uint2 *>(smem + PoolLds::adm);
   SlotRec *const s_slot = reinterpret_cast<SlotRec *>(smem + PoolLds::slot);
   uint4 *const s_win = reinterpret_cast<uint4 *>(smem + PoolLds::win);
   unsigned long long *const s_uc = reinterpret_cast<unsigned long long *>(smem + PoolLds::uc);
   int32_t *const s_xu = reinterpret_cast<int32_t *>(smem + PoolLds::xu);
-  int32_t *const s_sph = reinterpret_cast<int32_t *>(smem + PoolLds::sph);
-  int32_t *const s_spt = reinterpret_cast<int32_t *>(smem + PoolLds::spt);
+  uint32_t *const s_sph = reinterpret_cast<uint32_t *>(smem + PoolLds::sph);
+  uint32_t *const s_seg = reinterpret_cast<uint32_t *>(smem + PoolLds::seg);
+  uint32_t *const s_cap = reinterpret_cast<uint32_t *>(smem + PoolLds::cap);
   int32_t *const s_free = reinterpret_cast<int32_t *>(smem + PoolLds::freex);
   Ent *const cache = reinterpret_cast<Ent *>(smem + PoolLds::end);         // [M]
   int64_t *const u_lds = reinterpret_cast<int64_t *>(cache + M);           // [U]
-  uint16_t *const links = reinterpret_cast<uint16_t *>(u_lds + (ulds ? U : 0));  // [ML]
-  uint8_t *const u_rep = reinterpret_cast<uint8_t *>(links + ML);          // [tab]
+  uint8_t *const u_rep = reinterpret_cast<uint8_t *>(u_lds + (ulds ? U : 0));  // [tab]
   uint8_t *const st8 = u_rep + tab;                                        // [M + kStPad]
 
   const int64_t base = a.t.rep_off[r];
@@ -245,7 +249,8 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
   bool dirty = false;                           // calls were added: rank, pre to be taken again
   uint64_t nearm = 0, far = ~uint64_t(0);       // the calls ranked, the key they stay below
   int32_t nX = 0;                               // backlogged users (slots)
-  int32_t sp_total = 0, sp_low = 0;             // spilled calls, a lower bound of their records
+  int32_t n_adm = 0;                            // admissions staged in s_adm
+  int32_t sp_total = 0;                         // spilled calls
   int64_t minX = 0;
   int32_t code = 0;
   bool overflow = false;
@@ -292,6 +297,19 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     }
   };
 
+  // The staged admissions' fates, statuses and steps.
+  auto flush_admitted = [&]() {
+    char *const o_fate = reinterpret_cast<char *>(STATE(int8_t, fate) + base);
+    char *const o_status = reinterpret_cast<char *>(KARG(status) + base);
+    char *const o_step = reinterpret_cast<char *>(KARG(admit_step) + base);
+    for (int32_t i = lane; i < n_adm; i += 64) {
+      const uint2 e = s_adm[i];
+      o_fate[e.x] = 0;
+      o_status[e.x] = 0;
+      *reinterpret_cast<int32_t *>(o_step + (e.x << 2)) = int32_t(e.y);
+    }
+    n_adm = 0;
+  };
   // Throttled arrivals and the counters on arrival of the records before nxt.
   auto flush_window = [&](int32_t wb) {
     const int32_t done = nxt - wb;
@@ -315,20 +333,19 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
   // The lane standing for each window user and the lanes of the same user, through a table
   // indexed by the user's low bits (a user that lost its entry to another sends the window
   // to the matching bit by bit), then the slots of the users that are backlogged.
-  auto match_window = [&](int64_t c_u) {
+  auto match_window = [&](int32_t &xr, int32_t &xuser) {
     const bool wv = w_user >= 0;
     const uint64_t wvm = bal(wv);
     const int32_t hw = w_user & (tab - 1);
     if (wv) u_rep[hw] = uint8_t(lane);
-    s_win[lane] = make_uint4(uint32_t(uint64_t(c_u)), uint32_t(uint64_t(c_u) >> 32), 0xffffffffu, 0u);
     wave_fence();
-    const int32_t xuser = s_xu[lane];
+    xuser = s_xu[lane];
     const int32_t rr = wv ? int32_t(u_rep[hw]) & 63 : lane;
     const int32_t rx = int32_t(u_rep[xuser & (tab - 1)]) & 63;
     const int32_t rr_user = __builtin_amdgcn_ds_bpermute(rr << 2, w_user);
     const int32_t rx_user = __builtin_amdgcn_ds_bpermute(rx << 2, w_user);
     uint64_t g = wvm;
-    int32_t xr = -1;
+    xr = -1;
     if (!bal(wv && rr_user != w_user)) {
 #pragma unroll
       for (int b = 0; b < 6; ++b) {
@@ -352,14 +369,11 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     }
     w_gm = wv ? g : 0;
     w_ps = (w_gm & lt) ? 63 - __clzll((long long)(w_gm & lt)) : -1;
-    if (xuser >= 0) {
-      s_slot[lane].ext = (s_slot[lane].ext & ~kWinMask) | uint32_t(xr + 1);
-      if (xr >= 0) s_win[xr].z = uint32_t(lane);
-    }
-    wave_fence();
   };
 
-  // The window that starts at old (if any) is done; its throttled arrivals are written here.
+  // The window that starts at old (if any) is done: its throttled arrivals and the admissions
+  // since are written after the new window's dependent loads (before them when those read
+  // fates), so that no wait for a load also waits for these stores.
   auto load_window = [&](int32_t old) {
     wave_fence();
     const int32_t i = wbase + lane;
@@ -389,7 +403,6 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       f.why = (reason ? reason : reinterpret_cast<const uint8_t *>(T.len_in))[g];
       f.sc = LINKS ? reinterpret_cast<const int32_t *>(st + o_succ)[g] : -1;
     };
-    if (old >= cache_from) flush_window(old);  // (the fates below may be of these records)
     if (pf_at != wbase) fetch(i, pf);  // (the first window of the call)
     const RawRec c = pf;
     const bool in = i < n;
@@ -397,7 +410,13 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     const int32_t lo_ = wbase + 64 - M;
     cache_lo = lo_ > cache_from ? lo_ : cache_from;
     int8_t pf_fate = -1, hf_fate = -1;
-    if (LINKS && in && c.call > 0 && (c.pv < cache_lo || c.hd < cache_lo)) {
+    const bool aged = LINKS && in && c.call > 0 && (c.pv < cache_lo || c.hd < cache_lo);
+    const bool early = LINKS && bal(aged) != 0;
+    if (early) {
+      if (old >= cache_from) flush_window(old);
+      flush_admitted();
+    }
+    if (aged) {
       const int8_t *const fate = reinterpret_cast<const int8_t *>(st + o_fate) + base;
       pf_fate = ld_fresh(fate + c.pv);
       hf_fate = ld_fresh(fate + c.hd);
@@ -431,13 +450,25 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       if (in) st8[i & (M - 1)] = 0;  // undecided
     }
     if (in) cache[i & (M - 1)] = mk_ent(i, c.sc, w_lo, w_hi);
+    int32_t xr, xuser;
+    match_window(xr, xuser);  // (while the counters are on their way)
     // every loaded value is in its register from here on: no later wait on HBM
     __asm__ volatile("" ::"v"(w_step), "v"(w_user), "v"(w_why), "v"(w_head), "v"(w_prev),
                      "v"(w_succ), "v"(w_lo), "v"(w_hi), "v"(c_u));
+    if (!early) {
+      if (old >= cache_from) flush_window(old);
+      flush_admitted();
+    }
     // the next window's records, into the registers this window's just left
     pf_at = wbase + 64;
     fetch(pf_at + lane, pf);
-    match_window(c_u);
+    s_win[lane] = make_uint4(uint32_t(uint64_t(c_u)), uint32_t(uint64_t(c_u) >> 32), 0xffffffffu, 0u);
+    wave_fence();
+    if (xuser >= 0) {
+      s_slot[lane].ext = (s_slot[lane].ext & ~kWinMask) | uint32_t(xr + 1);
+      if (xr >= 0) s_win[xr].z = uint32_t(lane);
+    }
+    wave_fence();
   };
 
   // Ranks of the pooled calls.  With more than kNearMin of them, those from key `far` on are
@@ -458,8 +489,22 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     if (FS_RARE(wide || backlog >= (int64_t(1) << 26))) {
       pool_rank_wide(key, ua, tok, nearm, rank, pre);
     } else {
-      const uint64_t p = (rel << ksh) | (uint64_t(kh & kPTier1) << 32) | ua;
-      const uint32_t rp = pool_rank(p, tok, nearm, s_rank);
+      const bool nr = in_mask(nearm);
+      const uint64_t q = (rel << ksh) | (uint64_t(kh & kPTier1) << 32) | ua;
+      const uint64_t p = nr ? q : ~uint64_t(0);
+      uint32_t sh = uint32_t(p >> 32), sl = uint32_t(p), sa = nr ? tok | (1u << 26) : 0u;
+      int32_t top = 64 - __builtin_clzll(nearm);
+      if (LINKS && nearm != occ) {
+        // the calls ranked packed into the lowest lanes, the others (which count for nothing)
+        // above them
+        const int32_t nn = __popcll(nearm);
+        const int32_t to = (nr ? below(nearm) : nn + below(~nearm)) << 2;
+        sh = uint32_t(__builtin_amdgcn_ds_permute(to, int(sh)));
+        sl = uint32_t(__builtin_amdgcn_ds_permute(to, int(sl)));
+        sa = uint32_t(__builtin_amdgcn_ds_permute(to, int(sa)));
+        top = nn;
+      }
+      const uint32_t rp = pool_rank(p, sh, sl, sa, top);
       rank = rp >> 26;
       pre = rp & ((1u << 26) - 1);
     }
@@ -474,10 +519,31 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     }
     dirty = false;
   };
+  // Lane l was just added to calls whose ranks are known: its rank, and theirs after it.
+  auto rank_one = [&](int l) {
+    const uint64_t key = (uint64_t(kh) << 32) | kl;
+    const uint64_t kj = uint64_t(rdl64(int64_t(key), l));
+    const uint32_t uj = rdlu(ua, l), tok = q_lo & uint32_t(kTokMask), tj = rdlu(tok, l);
+    if (kj >= far) {  // not among the ranked
+      if (lane == l) {
+        rank = 0x7fffffffu;
+        pre = 0xffffffffu;
+      }
+      return;
+    }
+    const uint64_t gm = nearm & bal(key > kj || (key == kj && ua > uj));
+    const uint32_t c = uint32_t(__popcll(nearm & ~gm));
+    const uint32_t pj = gm ? rdlu(pre, first_of(gm & bal(rank == c)))
+                           : (c ? rdlu(pre + tok, first_of(nearm & bal(rank == c - 1))) : 0u);
+    const bool gt = in_mask(gm);
+    rank = lane == l ? c : (gt ? rank + 1 : rank);
+    pre = lane == l ? pj : (gt ? pre + tj : pre);
+    nearm |= uint64_t(1) << l;
+  };
   // A free pool lane takes call (rec, sc, lo, hi) of slot x with key k at position ah.
   auto place = [&](int32_t x, int32_t user, uint64_t k, int32_t ah, int32_t rec, int32_t sc,
-                   uint32_t lo, uint32_t hi) {
-    const int l = ff1(~occ);
+                   uint32_t lo, uint32_t hi) -> int {
+    const int l = first_of(~occ);
     occ |= uint64_t(1) << l;
     if (lane == l) {
       kh = uint32_t(k >> 32);
@@ -489,6 +555,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       q_lo = lo;
       q_hi = hi;
     }
+    return l;
   };
   // First call rec joins the end of slot x's pooled calls.
   auto append = [&](int32_t x, int32_t user, int32_t rec, int32_t sc, uint32_t lo, uint32_t hi) {
@@ -536,60 +603,105 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       s_slot[x].num = num + 1 + kRdyOne;
     }
     wave_fence();
-    place(x, user, k, ah, rec, sc, lo, hi);
-    dirty = true;
+    const bool all = nearm == occ;
+    const int l = place(x, user, k, ah, rec, sc, lo, hi);
+    if (am || dirty || !LINKS) {
+      dirty = true;
+    } else {
+      if (all) far = ~uint64_t(0);
+      rank_one(l);
+    }
   };
-  // The spill list of slot x: records in order, links[rec] the distance to the next one.
-  // A record's link stays valid while all spilled records lie within ML of each other
-  // (they are below the end of the window).  Can records from lo on be spilled?
-  auto spill_fits = [&](int32_t lo) -> bool {
-    if (sp_total == 0 || lo < sp_low) sp_low = lo;
-    if (wbase + 64 - sp_low < ML) return true;
-    const bool has = s_xu[lane] >= 0 && s_slot[lane].ext >= kSpOne;
-    const int32_t mn = int32_t(wave_min32(has ? uint32_t(s_sph[lane]) : 0x7fffffffu));
-    sp_low = mn < lo ? mn : lo;
-    return wbase + 64 - sp_low < ML;
+  // The spill list of a user: its first calls beyond the pool, in order, in the user's
+  // segment of the state buffer (a place per request of the user, used as a ring).  Its
+  // segment and places, read when the list of a slot without one starts.
+  auto seg_of = [&](int32_t user, bool has, int32_t x, uint32_t &sb, uint32_t &cap, uint32_t &head) {
+    if (has) {
+      sb = s_seg[x];
+      cap = s_cap[x];
+      head = s_sph[x];
+    } else {
+      const uint32_t *const ss = STATE(const uint32_t, seg_start) + int64_t(r) * U + user;
+      sb = ss[0];
+      cap = ss[1] - sb;
+      head = 0;
+      s_seg[x] = sb;
+      s_cap[x] = cap;
+      s_sph[x] = 0;
+    }
   };
-  auto spill_append = [&](int32_t x, int32_t rec) {
+  auto place_of = [&](uint32_t at, uint32_t cap) -> uint32_t { return at >= cap ? at - cap : at; };
+  auto spill_append = [&](int32_t x, int32_t user, int32_t rec, int32_t sc, uint32_t lo, uint32_t hi) {
     wave_fence();
     const uint32_t e = uint32_t(uni(int32_t(s_slot[x].ext)));
-    const int32_t t = uni(s_spt[x]);
     if (lane == 0) {
-      if (e >= kSpOne)
-        links[t & (ML - 1)] = uint16_t(rec - t);
-      else
-        s_sph[x] = rec;
-      s_spt[x] = rec;
+      uint32_t sb, cap, head;
+      seg_of(user, e >= kSpOne, x, sb, cap, head);
+      STATE(Ent, seg_pk)[int64_t(sb) + place_of(head + e / kSpOne, cap)] = mk_ent(rec, sc, lo, hi);
       s_slot[x].ext = e + kSpOne;
     }
     wave_fence();
     ++sp_total;
   };
-  // Up to `most` calls of slot x's spill list come back to the pool, in order.
-  auto spill_refill = [&](int32_t x, int32_t most) {
+  // Up to 16 calls of slot x's spill list come back to the pool, in order: one load.
+  auto spill_refill = [&](int32_t x) {
     wave_fence();
-    uint32_t e = uint32_t(uni(int32_t(s_slot[x].ext)));
-    int32_t h = uni(s_sph[x]);
+    const SlotRec e = s_slot[x];
+    const uint32_t ext = uint32_t(uni(int32_t(e.ext))), num = uint32_t(uni(int32_t(e.num)));
+    const uint32_t sb = s_seg[x], cap = s_cap[x], head = s_sph[x];
     const int32_t user = uni(s_xu[x]);
-    int32_t k = 0;
-    for (; k < most && e >= kSpOne && ~occ; ++k) {
-      int32_t sc;
-      uint32_t lo, hi;
-      fetch_rec(h, sc, lo, hi);
-      append(x, user, h, sc, lo, hi);
-      e -= kSpOne;
-      if (e >= kSpOne) h += int32_t(uni(int32_t(links[h & (ML - 1)])));
+    uint32_t m = ext / kSpOne;
+    if (m > 16) m = 16;
+    if (__popcll(occ) > kPoolRoom && m > uint32_t(kPoolShare)) m = kPoolShare;
+    if (m > uint32_t(64 - __popcll(occ))) m = uint32_t(64 - __popcll(occ));
+    if (m == 0) return;
+    const bool mine = uint32_t(lane) < m;
+    Ent v = mk_ent(-1, -1, 0, 0);
+    if (mine) v = STATE(Ent, seg_pk)[int64_t(sb) + place_of(head + uint32_t(lane), cap)];
+    // the counter before each: the costs of those before it, over the first 16 lanes
+    const uint64_t cst = ((uint64_t(v.hi) << 32) | v.lo) >> 24;
+    uint64_t sum = cst;
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) {
+      const int src = (lane >= d ? lane - d : lane) << 2;
+      const uint32_t lo = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(uint32_t(sum))));
+      const uint32_t hi = uint32_t(__builtin_amdgcn_ds_bpermute(src, int(uint32_t(sum >> 32))));
+      sum += lane >= d ? (uint64_t(hi) << 32) | lo : 0;
     }
-    if (lane == 0) {
-      s_slot[x].ext = e;
-      s_sph[x] = h;
+    const uint64_t pe = (uint64_t(e.phi) << 32) | e.plo;
+    const uint64_t k = pe + sum - cst;
+    if (mine) {
+      s_stage[2 * lane] = make_uint4(uint32_t(k >> 32) | kPTier1, uint32_t(k),
+                                     (uint32_t(user) << kAheadBits) | ((num & kNumMask) + uint32_t(lane)),
+                                     uint32_t(x));
+      s_stage[2 * lane + 1] = make_uint4(uint32_t(v.rec), uint32_t(v.succ), v.lo, v.hi);
     }
     wave_fence();
-    sp_total -= k;
+    const int32_t fi = below(~occ);
+    const uint64_t tm = bal(fi < int32_t(m)) & ~occ;
+    if (in_mask(tm)) {
+      const uint4 ea = s_stage[2 * fi], eb = s_stage[2 * fi + 1];
+      kh = ea.x;
+      kl = ea.y;
+      ua = ea.z;
+      qx = int32_t(ea.w);
+      q_rec = int32_t(eb.x);
+      q_succ = int32_t(eb.y);
+      q_lo = eb.z;
+      q_hi = eb.w;
+    }
+    occ |= tm;
+    if (uint32_t(lane) == m - 1) {
+      const uint64_t v1 = pe + sum;
+      s_slot[x] = SlotRec{uint32_t(v1), uint32_t(v1 >> 32), num + m, ext - m * kSpOne};
+      s_sph[x] = place_of(head + m, cap);
+    }
+    wave_fence();
+    sp_total -= int32_t(m);
+    dirty = true;
   };
   // The last pooled first call of every user with two or more pooled calls goes to the
-  // front of its user's spill list.  Returns the number of lanes freed (0: none, or a
-  // record too far from the other spilled ones).
+  // front of its user's spill list.  Returns the number of lanes freed.
   auto evict = [&]() -> int32_t {
     wave_fence();
     const bool oc = (occ >> lane) & 1;
@@ -598,13 +710,12 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     const bool ev = oc && (kh & kPTier1) && ah > 0 && ah == int32_t(e.num & kNumMask) - 1;
     const uint64_t em = bal(ev);
     if (!em) return 0;
-    if (!spill_fits(int32_t(wave_min32(ev ? uint32_t(q_rec) : 0x7fffffffu)))) return 0;
     if (ev) {
-      if (e.ext >= kSpOne)
-        links[q_rec & (ML - 1)] = uint16_t(s_sph[qx] - q_rec);
-      else
-        s_spt[qx] = q_rec;
-      s_sph[qx] = q_rec;
+      uint32_t sb, cap, head;
+      seg_of(int32_t(ua >> kAheadBits), e.ext >= kSpOne, qx, sb, cap, head);
+      head = head ? head - 1 : cap - 1;
+      STATE(Ent, seg_pk)[int64_t(sb) + head] = mk_ent(q_rec, q_succ, q_lo, q_hi);
+      s_sph[qx] = head;
       s_slot[qx] = SlotRec{kl, kh & ~kPTier1, e.num - 1, e.ext + kSpOne};
       kh = kl = ua = 0xffffffffu;
     }
@@ -636,6 +747,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     uint64_t padm = LINKS ? bal(ps == 1) & inbm : 0;
     const uint64_t hblk = LINKS ? bal(hs == 2) & inbm : 0;
     if (LINKS && FS_RARE((w_old & inbm) != 0)) {
+      flush_admitted();
       const int8_t *const fate = STATE(const int8_t, fate) + base;
       bool pa = false;
       if (in_mask(w_old & inbm)) pa = ld_fresh(fate + w_prev) == 0;
@@ -735,35 +847,21 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     uint64_t app = (F | rdym) & ~slow;  // calls appended to their users' pooled calls
     // a user's first calls stay together in order: behind spilled ones, or beyond the
     // share of the pool a user may hold while it is filling up, a call is spilled
-    if (FS_RARE(sp_total > 0 || held + need > 52)) {
-      const int32_t most = held + need <= 52 ? 52 : 3;
+    if (FS_RARE(sp_total > 0 || held + need > kPoolRoom)) {
+      const int32_t most = held + need <= kPoolRoom ? kPoolRoom : kPoolShare;
       const uint64_t sp = F & bal(e.ext >= kSpOne || cn + __popcll(same & F & lt) >= most);
       if (sp) {
-        if (spill_fits(wbase + first_of(sp))) {
-          app &= ~sp;
-          const uint64_t sm = same & sp;
-          const int32_t rec = wbase + lane;
-          const int32_t tl = s_spt[x & 63];
-          wave_fence();
-          if (in_mask(sp)) {
-            const uint64_t above = lane < 63 ? sm >> (lane + 1) : 0;
-            if (above) links[rec & (ML - 1)] = uint16_t(__ffsll((long long)above));
-            if ((sm & lt) == 0) {
-              if (e.ext >= kSpOne)
-                links[tl & (ML - 1)] = uint16_t(rec - tl);
-              else
-                s_sph[x] = rec;
-            }
-            if (!above) {
-              s_spt[x] = rec;
-              s_slot[x].ext = e.ext + uint32_t(__popcll(sm)) * kSpOne;
-            }
-          }
-          wave_fence();
-          sp_total += __popcll(sp);
-        } else if (F & bal(e.ext >= kSpOne)) {
-          overflow = true;  // (links would wrap: the replica is handed over after this batch)
+        app &= ~sp;
+        const uint64_t sm = same & sp;
+        if (in_mask(sp)) {
+          uint32_t sb, cap, head;
+          seg_of(w_user, e.ext >= kSpOne, x, sb, cap, head);
+          const uint32_t i = uint32_t(__popcll(sm & lt)), c = e.ext / kSpOne;
+          STATE(Ent, seg_pk)[int64_t(sb) + place_of(head + c + i, cap)] = mk_ent(wbase + lane, w_succ, w_lo, w_hi);
+          if ((sm >> lane) == 1) s_slot[x].ext = e.ext + (i + 1) * kSpOne;
         }
+        wave_fence();
+        sp_total += __popcll(sp);
       }
     }
     const bool isA = in_mask(app), isR = LINKS && in_mask(rdym);
@@ -876,21 +974,18 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
         }
         ready_insert(x, rec, sc, lo, hi);
       } else {
+        // (room is made first: the user's own last call may be one that goes)
+        const bool room = ~occ != 0 || evict() != 0;
         const SlotRec e = s_slot[x];
         const int32_t cn = uni(int32_t(e.num & kNumMask));
-        const bool many = cn >= (__popcll(occ) < 52 ? 52 : 2);
+        const bool many = cn >= (__popcll(occ) < kPoolRoom ? kPoolRoom : kPoolShare);
         if (uni(int32_t(e.ext)) >= int32_t(kSpOne) || many) {
-          if (!spill_fits(rec)) {
-            overflow = true;
-            break;
-          }
-          spill_append(x, rec);
-        } else {
-          if (!~occ && !evict()) {
-            overflow = true;
-            break;
-          }
+          spill_append(x, k, rec, sc, lo, hi);
+        } else if (room) {
           append(x, k, rec, sc, lo, hi);
+        } else {
+          overflow = true;
+          break;
         }
       }
     }
@@ -921,9 +1016,6 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     head_range(minX, mx);
     dirty = true;
   }
-  char *const o_fate = reinterpret_cast<char *>(STATE(int8_t, fate) + base);
-  char *const o_status = reinterpret_cast<char *>(KARG(status) + base);
-  char *const o_step = reinterpret_cast<char *>(KARG(admit_step) + base);
 
   // ---- steps.  One loop: a pass takes the arrivals of step s in the window, then a batch
   // of its admissions, then ends the step; it starts over for the next window, for fewer
@@ -992,8 +1084,8 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       const bool oc = in_mask(occ);
       const uint32_t tok = q_lo & uint32_t(kTokMask);
       const SlotRec e = s_slot[oc ? qx : 64];
-      if (dirty || (LINKS && !nearm)) take_ranks();
       moved = true;
+      if (dirty || (LINKS && !nearm)) take_ranks();
       const uint32_t bud = (budget >> 32) ? 0xffffffffu : uint32_t(budget);
       uint64_t fm = bal(pre < bud) & occ;
       if (LINKS && FS_RARE(fm == nearm && nearm != occ)) {  // all ranked calls fit: rank all
@@ -1029,10 +1121,10 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       }
       const int lastl = first_of(bal(rank == m - 1) & fm);  // the last admitted
       const uint32_t used = rdlu(pre + tok, lastl);
-      if (fin) {
-        o_fate[uint32_t(q_rec)] = 0;
-        o_status[uint32_t(q_rec)] = 0;
-        *reinterpret_cast<int32_t *>(o_step + (uint32_t(q_rec) << 2)) = s;
+      s_adm[fin ? n_adm + below(fm) : kOutStage] = make_uint2(uint32_t(q_rec), uint32_t(s));
+      n_adm += int32_t(m);
+      if (FS_RARE(n_adm > kOutStage - 64)) flush_admitted();
+      if (fin && (LINKS || want_seq)) {
         if (LINKS) st8[q_rec >= cache_lo ? (q_rec & (M - 1)) : M + kStPad - 1] = 1;
         if (want_seq) {  // (optional outputs)
           int32_t *const as = KARG(admit_seq);
@@ -1095,7 +1187,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
           fetch_rec(c_sc, s2, lo2, hi2);
           ready_insert(c_x, c_sc, s2, lo2, hi2);
         }
-        if (sp_total > 0 && uni(int32_t(s_slot[c_x].num & kNumMask)) == 0) spill_refill(c_x, 16);
+        if (sp_total > 0 && uni(int32_t(s_slot[c_x].num & kNumMask)) == 0) spill_refill(c_x);
         continue;
       }
     }
@@ -1125,6 +1217,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
 
   if (code) raise_err(a.err, code);
   if (wbase >= cache_from) flush_window(wbase);
+  flush_admitted();
 
   // ---- save: counters of queued users back to u; the queue itself is rebuilt from
   // the records that have arrived and are still undecided
