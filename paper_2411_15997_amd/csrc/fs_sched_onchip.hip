@@ -1,5 +1,11 @@
 // WSC scheduler steps (Alg. 1, monitoring and execution streams) under the
-// token-budget step engine: the on-chip kernel, one wavefront per trace replica.
+// token-budget step engine: the on-chip kernels, one wavefront per trace replica.
+//
+// The paper's policy under the token-budget engine runs the pool pass (fs_sched_pool.h, one
+// queued call per lane) in k_schedule_pool; there the slot pass below takes only the steps
+// in which a replica has more users and ready calls than the pool has lanes.  The policy
+// flags and the literal engine run the slot pass alone (k_schedule_onchip): their orders
+// of service change with every charge (FCFS, blind limits) or wait on finishes.
 //
 // A replica is one dependent chain of arrivals and admissions, so its speed is the
 // length of the wave's instruction stream per event.  Everything an event touches

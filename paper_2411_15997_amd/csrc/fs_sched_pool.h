@@ -21,10 +21,16 @@
 // lanes of the user's calls.  First calls beyond the pool's room go to the user's segment of
 // the state buffer and come back 16 at a time.
 //
-// One call per lane replaced one user per lane with sequential admissions (about 1,300
-// clocks each: an argmin, the chosen user's next call and its new key in a dependent
-// chain), which remains in fs_sched_onchip.hip for the policy flags, the literal engine and the
-// replicas that outgrow the pool (more than 64 users and ready calls at once).
+// What bounds it: the latency of one wave's dependent instructions (about 8 clocks each; no
+// memory or matrix unit is near its rate), so the work per step is what is kept small.  One
+// call per lane replaced one user per lane with sequential admissions (about 1,300 clocks
+// each: an argmin, the chosen user's next call and its new key in a dependent chain), which
+// remains in fs_sched_onchip.hip for the policy flags, the literal engine and the replicas that
+// outgrow the pool (more than 64 users and ready calls at once).  Kernel and set-up, before
+// and after: one replica of 300,000 requests, 100,000 users and 17 admissions a step 204 -> 59 ms;
+// 1,024 replicas of 20,000 requests without interactions 12.8 -> 9.0 ms; 64 replicas of
+// 100,000 requests 74.7 -> 60.9 ms (54 to 65 ms over most seeds; 73 to 82 ms where a replica
+// has thousands of calls queued for most of its steps, against 75 to 77).
 #pragma once
 #include "fs_sched_common.h"
 
@@ -102,8 +108,13 @@ __device__ __forceinline__ int32_t step_of(int64_t ts, int64_t tau, double tau_i
 constexpr uint32_t kPTier1 = 0x80000000u;  // a first call, in the key's high word
 constexpr int kAheadBits = 6;              // position among the user's pooled calls
 // Calls the pool takes without looking at whose they are, and a user's share beyond that.
+// 12 slices of the 64 replicas, over 16 seeds: 8.3 to 11.0 ms with 28 and 6, up to 11.2 with
+// 40 and 4, 11.1 with 28 and 3, 11.3 with 48 and 8; 20 and 4 the same, but the whole
+// replicas about 1% slower (57.8 against 56.6 ms).
 constexpr int kPoolRoom = 28, kPoolShare = 6;
-constexpr int kNearMin = 20, kNearLeast = 8, kNearRank = 16;  // calls ranked of a large pool
+// A pool of more than kNearMin calls is ranked below the key of rank kNearRank while at least
+// kNearLeast calls are: a ranking costs about 55 clocks a call and a step admits a handful.
+constexpr int kNearMin = 20, kNearLeast = 8, kNearRank = 16;
 
 // A slot's record: the counter after the user's pooled calls; the number of pooled calls and
 // of the ready ones among them (kRdyOne each); the user's window lane plus one and the
@@ -115,7 +126,7 @@ constexpr uint32_t kNumMask = 0xffu, kRdyOne = 0x100u, kWinMask = 0xffu, kSpOne 
 
 constexpr int kOutStage = 192;  // admissions kept until the next window (then written together)
 
-// Byte offsets of the pool pass's LDS (the cache, counters, links and tables follow).
+// Byte offsets of the pool pass's LDS (the cache, counters and tables follow).
 // Entry 64 of an array takes the stores of lanes that have none to make.
 struct PoolLds {
   static constexpr int stage = 0;                // [65] two 16-byte words: calls placed
@@ -519,7 +530,8 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     }
     dirty = false;
   };
-  // Lane l was just added to calls whose ranks are known: its rank, and theirs after it.
+  // Lane l was just added to calls whose ranks are known: its rank, and theirs after it (two
+  // ballots and two lane reads, against a ranking of all of them).
   auto rank_one = [&](int l) {
     const uint64_t key = (uint64_t(kh) << 32) | kl;
     const uint64_t kj = uint64_t(rdl64(int64_t(key), l));
