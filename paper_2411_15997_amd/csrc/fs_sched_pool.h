@@ -1136,17 +1136,17 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       s_adm[fin ? n_adm + below(fm) : kOutStage] = make_uint2(uint32_t(q_rec), uint32_t(s));
       n_adm += int32_t(m);
       if (FS_RARE(n_adm > kOutStage - 64)) flush_admitted();
-      if (fin && (LINKS || want_seq)) {
+      if (fin && (LINKS || want_seq || want_coa)) {
         if (LINKS) st8[q_rec >= cache_lo ? (q_rec & (M - 1)) : M + kStPad - 1] = 1;
         if (want_seq) {  // (optional outputs)
           int32_t *const as = KARG(admit_seq);
           int64_t *const ca = KARG(counter_after);
           if (as) as[base + q_rec] = seq + int32_t(rank);
           if (ca) ca[base + q_rec] = int64_t(unew);
-          if (want_coa)
-            __hip_atomic_fetch_max(s_uc + qx, (unsigned long long)unew, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         }
+        if (want_coa)  // (the user's counter for its next arrivals, whatever else is asked for)
+          __hip_atomic_fetch_max(s_uc + qx, (unsigned long long)unew, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
       }
       budget -= int64_t(used);
       backlog -= int64_t(used);
