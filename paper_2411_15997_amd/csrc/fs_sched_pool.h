@@ -1099,11 +1099,12 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       moved = true;
       if (dirty || (LINKS && !nearm)) take_ranks();
       const uint32_t bud = (budget >> 32) ? 0xffffffffu : uint32_t(budget);
-      uint64_t fm = bal(pre < bud) & occ;
+      // (of the ranked calls: `pre` of the others starts at all ones and falls with every batch)
+      uint64_t fm = bal(pre < bud) & (LINKS ? nearm : occ);
       if (LINKS && FS_RARE(fm == nearm && nearm != occ)) {  // all ranked calls fit: rank all
         far = 0;
         take_ranks();
-        fm = bal(pre < bud) & occ;
+        fm = bal(pre < bud) & nearm;
       }
       const int32_t ah = int32_t(ua & 63u), cn = int32_t(e.num & kNumMask);
       const uint64_t tailm = bal(ah == cn - 1);

@@ -59,3 +59,34 @@ def test_pool_outgrown_and_taken_back():
     for theta in (10 ** 9, 200, -1):
         say("pool taken back", theta)
         _check(tr, cost, reason, 100, 12, theta, 301)
+
+
+@pytest.mark.parametrize("length", [20, 80])
+def test_pool_long_drain_of_chains(length):
+    """More than 2^32 tokens admitted between two rankings of the pool, while some of its
+    calls are outside the ranking: 12 chains whose calls have all arrived (each admitted call
+    makes the next one ready, which takes its rank in place) over 41 queued first calls.  A
+    step admits one or two calls of up to 2^24 - 1 tokens; the second ranking, after a full one
+    and new arrivals, leaves the first calls out."""
+    rng = np.random.default_rng(length)
+    chains, plain, C = 12, 41, 3 << 22
+    rows = [(0, u, 0, 10) for u in range(chains)]  # (step, user, call, tokens); admitted in step 0
+    rows += [(1, chains + k, 0, 1000 + k) for k in range(plain - 1)]
+    rows += [(1, u, 1, int(rng.integers(1 << 23, 1 << 24))) for u in range(chains)]
+    rows += [(2, chains + plain - 1, 0, 1000)]
+    rows += [(2, u, c, int(rng.integers(1 << 23, 1 << 24))) for c in range(2, length) for u in range(chains)]
+    at = {}
+    n = len(rows)
+    user, call, tok, ts = (np.zeros(n, np.int32) for _ in range(4))
+    head, prev = np.arange(n, dtype=np.int32), np.full(n, -1, np.int32)
+    for i, (step, u, c, t) in enumerate(rows):
+        user[i], call[i], tok[i], ts[i] = u, c, t, step * 10
+        if c > 0:
+            head[i], prev[i] = at[u, 0], at[u, c - 1]
+        at[u, c] = i
+    z = np.zeros(n, np.int32)
+    tr = tg.Trace(1, chains + plain, 1, np.array([0, n], np.int64), ts.astype(np.int64), user, z.copy(),
+                  call, head, prev, tok, None, z.copy())
+    cost = rng.integers(1, 900, n).astype(np.int64)
+    say("pool long drain", length)
+    _check(tr, cost, np.zeros(n, np.uint8), 10, C, 10 ** 12, 301)
