@@ -116,13 +116,14 @@ constexpr int kPoolRoom = 28, kPoolShare = 6;
 // kNearLeast calls are: a ranking costs about 55 clocks a call and a step admits a handful.
 constexpr int kNearMin = 20, kNearLeast = 8, kNearRank = 16;
 
-// A slot's record: the counter after the user's pooled calls; the number of pooled calls and
-// of the ready ones among them (kRdyOne each); the user's window lane plus one and the
-// number of spilled calls (kSpOne each).
+// A slot's record: the counter after the user's pooled calls; the number of pooled calls, of
+// the ready ones among them (kRdyOne each) and the user's window lane plus one (kWinOne
+// each), all at most 64; the number of spilled calls (as many as the replica has records).
 struct __align__(16) SlotRec {
-  uint32_t plo, phi, num, ext;
+  uint32_t plo, phi, num, spilled;
 };
-constexpr uint32_t kNumMask = 0xffu, kRdyOne = 0x100u, kWinMask = 0xffu, kSpOne = 0x100u;
+constexpr uint32_t kNumMask = 0xffu, kRdyOne = 0x100u, kWinOne = 0x1000000u;
+__device__ __forceinline__ uint32_t ready_of(uint32_t num) { return (num / kRdyOne) & kNumMask; }
 
 constexpr int kOutStage = 192;  // admissions kept until the next window (then written together)
 
@@ -476,7 +477,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     s_win[lane] = make_uint4(uint32_t(uint64_t(c_u)), uint32_t(uint64_t(c_u) >> 32), 0xffffffffu, 0u);
     wave_fence();
     if (xuser >= 0) {
-      s_slot[lane].ext = (s_slot[lane].ext & ~kWinMask) | uint32_t(xr + 1);
+      s_slot[lane].num = (s_slot[lane].num & (kWinOne - 1)) | uint32_t(xr + 1) * kWinOne;
       if (xr >= 0) s_win[xr].z = uint32_t(lane);
     }
     wave_fence();
@@ -645,12 +646,12 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
   auto place_of = [&](uint32_t at, uint32_t cap) -> uint32_t { return at >= cap ? at - cap : at; };
   auto spill_append = [&](int32_t x, int32_t user, int32_t rec, int32_t sc, uint32_t lo, uint32_t hi) {
     wave_fence();
-    const uint32_t e = uint32_t(uni(int32_t(s_slot[x].ext)));
+    const uint32_t e = uint32_t(uni(int32_t(s_slot[x].spilled)));
     if (lane == 0) {
       uint32_t sb, cap, head;
-      seg_of(user, e >= kSpOne, x, sb, cap, head);
-      STATE(Ent, seg_pk)[int64_t(sb) + place_of(head + e / kSpOne, cap)] = mk_ent(rec, sc, lo, hi);
-      s_slot[x].ext = e + kSpOne;
+      seg_of(user, e != 0, x, sb, cap, head);
+      STATE(Ent, seg_pk)[int64_t(sb) + place_of(head + e, cap)] = mk_ent(rec, sc, lo, hi);
+      s_slot[x].spilled = e + 1;
     }
     wave_fence();
     ++sp_total;
@@ -659,10 +660,10 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
   auto spill_refill = [&](int32_t x) {
     wave_fence();
     const SlotRec e = s_slot[x];
-    const uint32_t ext = uint32_t(uni(int32_t(e.ext))), num = uint32_t(uni(int32_t(e.num)));
+    const uint32_t spilled = uint32_t(uni(int32_t(e.spilled))), num = uint32_t(uni(int32_t(e.num)));
     const uint32_t sb = s_seg[x], cap = s_cap[x], head = s_sph[x];
     const int32_t user = uni(s_xu[x]);
-    uint32_t m = ext / kSpOne;
+    uint32_t m = spilled;
     if (m > 16) m = 16;
     if (__popcll(occ) > kPoolRoom && m > uint32_t(kPoolShare)) m = kPoolShare;
     if (m > uint32_t(64 - __popcll(occ))) m = uint32_t(64 - __popcll(occ));
@@ -705,7 +706,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     occ |= tm;
     if (uint32_t(lane) == m - 1) {
       const uint64_t v1 = pe + sum;
-      s_slot[x] = SlotRec{uint32_t(v1), uint32_t(v1 >> 32), num + m, ext - m * kSpOne};
+      s_slot[x] = SlotRec{uint32_t(v1), uint32_t(v1 >> 32), num + m, spilled - m};
       s_sph[x] = place_of(head + m, cap);
     }
     wave_fence();
@@ -724,11 +725,11 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     if (!em) return 0;
     if (ev) {
       uint32_t sb, cap, head;
-      seg_of(int32_t(ua >> kAheadBits), e.ext >= kSpOne, qx, sb, cap, head);
+      seg_of(int32_t(ua >> kAheadBits), e.spilled != 0, qx, sb, cap, head);
       head = head ? head - 1 : cap - 1;
       STATE(Ent, seg_pk)[int64_t(sb) + head] = mk_ent(q_rec, q_succ, q_lo, q_hi);
       s_sph[qx] = head;
-      s_slot[qx] = SlotRec{kl, kh & ~kPTier1, e.num - 1, e.ext + kSpOne};
+      s_slot[qx] = SlotRec{kl, kh & ~kPTier1, e.num - 1, e.spilled + 1};
       kh = kl = ua = 0xffffffffu;
     }
     wave_fence();
@@ -833,8 +834,8 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
       nX += __popcll(jm);
       const int32_t xd = jl ? xs : 64;
       s_xu[xd] = w_user;
-      s_slot[xd] = SlotRec{uint32_t(uint64_t(lifted)), uint32_t(uint64_t(lifted) >> 32), 0u,
-                           uint32_t(w_rep + 1)};
+      s_slot[xd] = SlotRec{uint32_t(uint64_t(lifted)), uint32_t(uint64_t(lifted) >> 32),
+                           uint32_t(w_rep + 1) * kWinOne, 0u};
       s_win[jl ? w_rep : 64].z = uint32_t(xs);
       if (want_coa) s_uc[xd] = uint64_t(lifted);
       x = jl ? xs : x;
@@ -852,7 +853,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     // when none of those is a first call, else one at a time below
     uint64_t slow = 0;
     if (LINKS && rdym) {
-      slow = bal(int32_t(e.num >> 8) != cn);
+      slow = bal(int32_t(ready_of(e.num)) != cn);
       if (dup) slow |= bal((same & F & lt) != 0);
       slow &= rdym;
     }
@@ -861,16 +862,16 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     // share of the pool a user may hold while it is filling up, a call is spilled
     if (FS_RARE(sp_total > 0 || held + need > kPoolRoom)) {
       const int32_t most = held + need <= kPoolRoom ? kPoolRoom : kPoolShare;
-      const uint64_t sp = F & bal(e.ext >= kSpOne || cn + __popcll(same & F & lt) >= most);
+      const uint64_t sp = F & bal(e.spilled != 0 || cn + __popcll(same & F & lt) >= most);
       if (sp) {
         app &= ~sp;
         const uint64_t sm = same & sp;
         if (in_mask(sp)) {
           uint32_t sb, cap, head;
-          seg_of(w_user, e.ext >= kSpOne, x, sb, cap, head);
-          const uint32_t i = uint32_t(__popcll(sm & lt)), c = e.ext / kSpOne;
+          seg_of(w_user, e.spilled != 0, x, sb, cap, head);
+          const uint32_t i = uint32_t(__popcll(sm & lt)), c = e.spilled;
           STATE(Ent, seg_pk)[int64_t(sb) + place_of(head + c + i, cap)] = mk_ent(wbase + lane, w_succ, w_lo, w_hi);
-          if ((sm >> lane) == 1) s_slot[x].ext = e.ext + (i + 1) * kSpOne;
+          if ((sm >> lane) == 1) s_slot[x].spilled = c + i + 1;
         }
         wave_fence();
         sp_total += __popcll(sp);
@@ -991,7 +992,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
         const SlotRec e = s_slot[x];
         const int32_t cn = uni(int32_t(e.num & kNumMask));
         const bool many = cn >= (__popcll(occ) < kPoolRoom ? kPoolRoom : kPoolShare);
-        if (uni(int32_t(e.ext)) >= int32_t(kSpOne) || many) {
+        if (uni(int32_t(e.spilled)) != 0 || many) {
           spill_append(x, k, rec, sc, lo, hi);
         } else if (room) {
           append(x, k, rec, sc, lo, hi);
@@ -1113,7 +1114,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
         // a call whose next call has arrived, or a user's last pooled call before spilled
         // ones, ends the batch
         uint64_t cutm = LINKS ? bal(uint32_t(q_succ) < uint32_t(nxt)) : 0;
-        if (sp_total > 0) cutm |= tailm & bal(e.ext >= kSpOne);
+        if (sp_total > 0) cutm |= tailm & bal(e.spilled != 0);
         cutm &= fm;
         if (cutm) {
           const uint32_t rc = wave_min32(in_mask(cutm) ? rank : 0xffffffffu);
@@ -1174,7 +1175,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
         last_exit = int32_t(rdlu(ua, ll) >> kAheadBits);
         last_exit_u = rdl64(int64_t(unew), ll);
         const bool lv = in_mask(lm);
-        const uint32_t w = e.ext & kWinMask;
+        const uint32_t w = e.num / kWinOne;
         uint4 *const we = s_win + (lv && w ? w - 1 : 64);
         we->x = uint32_t(unew);
         we->y = uint32_t(unew >> 32);

@@ -4,8 +4,10 @@ links, chains whose next call waits, ties of zero-cost calls, keys too far apart
 order word, and the hand-over to the slot pass and back; in one call and in slices."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import paper_2411_15997_amd as fs
 from gpu_common import compare_sim, gpu_schedule, say
 from tiny import random_trace
 import tracegen as tg
@@ -90,3 +92,57 @@ def test_pool_long_drain_of_chains(length):
     cost = rng.integers(1, 900, n).astype(np.int64)
     say("pool long drain", length)
     _check(tr, cost, np.zeros(n, np.uint8), 10, C, 10 ** 12, 301)
+
+
+def _burst(queued):
+    """Every request arrives at once: `queued` calls of user 0, four calls each of 60 others
+    (they fill the pool, so that user 0's pooled calls are spilled as well), 50 of user 0."""
+    rng = np.random.default_rng(queued)
+    user = np.concatenate([np.zeros(queued, np.int32), np.tile(np.arange(1, 61, dtype=np.int32), 4),
+                           np.zeros(50, np.int32)])
+    n = user.size
+    z = np.zeros(n, np.int32)
+    tr = tg.Trace(1, 61, 1, np.array([0, n], np.int64), np.zeros(n, np.int64), user, z, None, None, None,
+                  rng.integers(0, 8, n).astype(np.int32), None, z)
+    return tr, rng.integers(0, 4000, n).astype(np.int64)
+
+
+def _burst_reference(tr, cost, cap):
+    """Admission order, step and counter after each call of such a burst in closed form: the
+    least counter is always served next, so the order is that of (counter before the call,
+    user, position), and the call with t tokens admitted before it is admitted in step t // cap
+    (overshoot is carried as debt).  (The oracle takes 25 s for 2^24 queued calls of one user.)"""
+    n = tr.n
+    after = np.zeros(n, np.int64)
+    for u in range(tr.n_users):
+        m = tr.user == u
+        after[m] = np.cumsum(cost[m])
+    order = np.lexsort((tr.user, after - cost))  # (stable: a user's calls stay in order)
+    seq, step = np.zeros(n, np.int32), np.zeros(n, np.int32)
+    seq[order] = np.arange(n)
+    before = np.cumsum(tr.len_in[order].astype(np.int64)) - tr.len_in[order]
+    step[order] = before // cap
+    return seq, step, after
+
+
+@pytest.mark.parametrize("queued,sliced", [(3000, True), ((1 << 23) + 100, True), ((1 << 24) + 100, False)])
+def test_pool_many_spilled_calls_of_one_user(queued, sliced):
+    """2^23 and 2^24 queued calls of one user: their order holds while the queue grows, while it
+    is rebuilt by a second call, and while it drains."""
+    tr, cost = _burst(queued)
+    cap = 4096 if queued < 10_000 else 1 << 20
+    seq, step, after = _burst_reference(tr, cost, cap)
+    if queued < 10_000:  # the closed form is the oracle's schedule
+        o = oracle.simulate(tr, cost, None, 10, cap, 10 ** 12)
+        assert (o.admit_seq == seq).all() and (o.admit_step == step).all() and (o.counter_after == after).all()
+    say("pool many spilled", queued, sliced)
+    dt = fs.DeviceTrace(tr)
+    c, eng, out, st = torch.as_tensor(cost).cuda(), fs.make_engine(10, cap, 10 ** 12), fs.Outputs(dt), fs.fs_state_init(dt)
+    for n_steps in ((1, -1) if sliced else (-1,)):
+        fs.fs_schedule_step(dt, st, c, None, eng, out, n_steps)
+        say("steps so far", int(out.steps[0]))
+    h = out.host()
+    assert (h["status"] == 0).all()
+    for k, want in (("admit_seq", seq), ("admit_step", step), ("counter_after", after)):
+        bad = np.nonzero(h[k] != want)[0]
+        assert bad.size == 0, (k, bad.size, bad[:5], h[k][bad[:5]], want[bad[:5]])
