@@ -124,9 +124,19 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
   // literal engine: the running batch and the KV tokens it holds
   int64_t kv_used = LITERAL ? uni64(rs->kv_used) : 0;
   int32_t n_run = LITERAL ? int32_t(uni64(rs->n_run)) : 0;
-  // stopped inside a step, or a batch larger than the LDS one: only the global-memory
-  // kernel resumes that
-  if (uni(rs->mid) || n_run > BQ) {
+  // stopped inside a step, a batch larger than the LDS one, or a running call that the
+  // global-memory kernel admitted since it does not fit a packed request: only that kernel
+  // resumes those
+  bool big_run = false;
+  if (LITERAL && n_run <= BQ) {
+    const int32_t *const rr_ = STATE(const int32_t, run_rec) + base + r;
+    for (int32_t i = lane; i < n_run; i += 64) {
+      const int64_t g = base + rr_[i];
+      const int32_t tok = a.t.len_in[g] + a.t.len_out[g] + (a.t.len_sys ? a.t.len_sys[g] : 0);
+      big_run = big_run || !fits_packed(a.cost[g], tok);
+    }
+  }
+  if (uni(rs->mid) || n_run > BQ || bal(big_run)) {
     if (lane == 0) {
       rs->overflow = 1;
       rs->s_end = s_end;
@@ -351,15 +361,18 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     return x;
   };
   // Data of an arrived record read from the inputs (when it is no longer cached).
-  auto load_rec = [&](int32_t i, int32_t &sc, uint32_t &lo, uint32_t &hi) {
+  // (false: it does not fit a packed request)
+  auto load_rec = [&](int32_t i, int32_t &sc, uint32_t &lo, uint32_t &hi) -> bool {
     const int64_t g = base + i;
     const int32_t *len_sys = KARG(t.len_sys);
     const int32_t tok =
         KARG(t.len_in)[g] + KARG(t.len_out)[g] + (len_sys ? len_sys[g] : 0);
-    const uint64_t pk = (uint64_t(KARG(cost)[g]) << 24) | uint32_t(tok);
+    const int64_t cst = KARG(cost)[g];
+    const uint64_t pk = (uint64_t(cst) << 24) | uint32_t(tok);
     sc = uni(STATE(const int32_t, succ)[base + i]);
     lo = uint32_t(uni(int32_t(uint32_t(pk))));
     hi = uint32_t(uni(int32_t(uint32_t(pk >> 32))));
+    return fits_packed(cst, tok);
   };
 
   // ---- admissions waiting to be written: lane i holds the i-th of nd
@@ -522,7 +535,8 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       if (LINKS && call > 0)
         fl |= (pf_fate == 0 ? kPrevAdm : 0) | ((hf_fate == 1 || hf_fate == 2) ? kHeadBlk : 0) |
               (pf_fate > 0 ? kPrevDrop : 0);
-      fl |= (why << kReasonShift) | (cst >= kPackLimit ? kBig : 0);
+      fl |= why << kReasonShift;
+      if (!fits_packed(cst, tok)) fl |= kBig;
       const int64_t stp = ts / tau;
       w_step = stp < INT32_MAX ? int32_t(stp) : INT32_MAX;
       w_user = usr;
@@ -800,10 +814,9 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       const int32_t call = callp ? uni(callp[g]) : 0;
       int32_t sc;
       uint32_t lo, hi;
-      load_rec(rec, sc, lo, hi);
+      const bool big = !load_rec(rec, sc, lo, hi);
       const bool padm = !fcfs && call > 0 && ld_fresh(fate + uni(KARG(t.prev)[g])) == 0;
       const uint64_t fm = bal(xu == k);
-      const bool big = KARG(cost)[g] >= kPackLimit;
       if (big || (fm == 0 && nX == kSlots) || (padm && pocc == ~uint64_t(0))) {
         overflow = true;  // nothing in the state buffer has changed yet
         break;

@@ -40,12 +40,17 @@ namespace {
 
 constexpr int64_t kPackLimit = int64_t(1) << 40;  // costs that fit a packed request
 constexpr uint64_t kTokMask = (uint64_t(1) << 24) - 1;
+// Whether a call fits a packed request, (cost << 24) | tokens (its three lengths, each below
+// 2^24, may sum to more); one that does not is taken by the global-memory pass.
+__device__ __forceinline__ bool fits_packed(int64_t cst, int32_t tok) {
+  return ((uint64_t(cst) / uint64_t(kPackLimit)) | (uint32_t(tok) >> 24)) == 0;  // (cst >= 0)
+}
 // window flags
 constexpr int32_t kFirst = 1;        // first call of its interaction
 constexpr int32_t kReasonShift = 1;  // bits 1-2: raw throttle reason (0 within limits)
 constexpr int32_t kHeadBlk = 8;      // later call whose interaction's first call was throttled
 constexpr int32_t kPrevAdm = 16;     // later call whose previous call has been admitted
-constexpr int32_t kBig = 32;         // cost too large for a packed request
+constexpr int32_t kBig = 32;         // does not fit a packed request
 constexpr int32_t kPrevDrop = 64;    // later call whose previous call was dropped
 
 // A queued request on chip: record, its next call (-1: none), (cost << 24) | tokens.
@@ -274,7 +279,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
   int32_t w_pst = 0, w_hst = 0;  // the previous and first calls' entries in st8
   uint32_t w_lo = 0, w_hi = 0, w_tsum = 0;  // w_tsum: tokens of the window up to the lane
   uint64_t w_first = 0, w_over = 0, w_big = 0, w_old = 0;  // masks of window lanes: first
-  // calls, those over a limit, costs too large for a packed request, later calls whose
+  // calls, those over a limit, those that do not fit a packed request, later calls whose
   // previous call is older than the cache and was undecided when the window was loaded
   int32_t w_rep = lane;  // the lane that stands for the window lanes of this user
   uint64_t w_gm = 0;     // the window lanes of this lane's user
@@ -448,7 +453,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     const bool first = c.call == 0;
     w_first = bal(in && first);
     w_over = bal(in && first && why != 0);
-    w_big = bal(in && c.cst >= kPackLimit);
+    w_big = bal(in && !fits_packed(c.cst, tok));
     if (LINKS) {
       const bool later = in && !first;
       w_pst = M + kStNone;
@@ -952,7 +957,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     const int64_t uv = ulds ? u_lds[ku] : ld_fresh(u_all + ku);
     const bool padm = q && call > 0 && ld_fresh(fate + (pv >= 0 ? pv : 0)) == 0;
     const uint64_t pk = (uint64_t(cst) << 24) | uint32_t(tok);
-    const uint64_t bigm = bal(q && cst >= kPackLimit);
+    const uint64_t bigm = bal(q && !fits_packed(cst, tok));
     const uint64_t padmm = bal(padm), laterm = bal(call > 0);
     if (bigm) overflow = true;
     while (m && !overflow) {
