@@ -4,7 +4,7 @@
 // the graph-size table (Table 2).  HBM-bound streaming passes; every accumulation is
 // an integer atomic (order-independent, so results are deterministic), aggregated per
 // wave over the lanes that share a key before it reaches memory.
-//   1. k_ws_records_hash (k_ws_records for many apps)
+//   1. k_ws_records_hash (k_ws_records for many apps, or more keys than 32 bits)
 //                     per request: validity, the replica's latest arrival, requests and
 //                     tokens per (replica, user, app), the length histograms and sums per
 //                     (replica, app) (in LDS per work-group and replica segment), and one
@@ -268,9 +268,18 @@ __global__ void __launch_bounds__(kRecThreads) k_ws_records_hash(WsArgs a) {
   if (code) raise_err(a.err, code);
 }
 
-// The records pass for more applications than an LDS table takes, or more (replica, user,
-// app) keys than 32 bits: aggregated per wave.
+// The records pass for more (replica, user, app) keys than 32 bits, or more applications than
+// the tables take: requests and tokens aggregated per wave; the apps' length histograms and
+// sums in LDS while they fit (LDS), else per wave too.
+struct WaveLds {
+  uint32_t lh[kLdsApps * 3 * kLenBins];     // length histograms [A][3][bins]
+  unsigned long long ls[kLdsApps * 3];      // length sums [A][3]
+  unsigned long long red[kThreads / 64];    // per-wave maxima
+};
+
+template <bool LDS>
 __global__ void __launch_bounds__(kThreads) k_ws_records(WsArgs a) {
+  __shared__ WaveLds sm;
   const DevTrace &t = a.t;
   int32_t code = 0;
   unsigned long long *const lh = reinterpret_cast<unsigned long long *>(a.o.len_hist);
@@ -278,12 +287,17 @@ __global__ void __launch_bounds__(kThreads) k_ws_records(WsArgs a) {
   const int64_t c0 = blockIdx.x * int64_t(a.chunk);
   const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
   const int32_t A = t.A;
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (LDS) {
+    for (int k = threadIdx.x; k < A * 3 * kLenBins; k += kThreads) sm.lh[k] = 0;
+    for (int k = threadIdx.x; k < A * 3; k += kThreads) sm.ls[k] = 0;
+  }
   int32_t r = c0 < c1 ? replica_of(t.rep_off, t.R, c0) : 0;
   for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
     while (t.rep_off[r + 1] <= s0) ++r;  // (empty replicas)
     const int64_t base = t.rep_off[r];
     const int64_t s1 = t.rep_off[r + 1] < c1 ? t.rep_off[r + 1] : c1;
+    __syncthreads();
     unsigned long long mts = 0;
     bool any = false;
     // whole waves step through the segment so that every lane joins the reductions
@@ -318,20 +332,49 @@ __global__ void __launch_bounds__(kThreads) k_ws_records(WsArgs a) {
                       a.ua_req, a.ua_tok);
 #pragma unroll
       for (int x = 0; x < 3; ++x) {
-        const int64_t ra = (int64_t(r) * A + ap) * 3 + x;
-        wave_add2<true>(ok, ra * kLenBins + len_bin(L[x]), 1ull, 0ull, lh, nullptr);
-        wave_add2<false>(ok && L[x] != 0, ra, (unsigned long long)L[x], 0ull, lsum, nullptr);
+        if (LDS) {
+          if (ok) {
+            atomicAdd(&sm.lh[(ap * 3 + x) * kLenBins + len_bin(L[x])], 1u);
+            if (L[x]) atomicAdd(&sm.ls[ap * 3 + x], (unsigned long long)L[x]);
+          }
+        } else {
+          const int64_t ra = (int64_t(r) * A + ap) * 3 + x;
+          wave_add2<true>(ok, ra * kLenBins + len_bin(L[x]), 1ull, 0ull, lh, nullptr);
+          wave_add2<false>(ok && L[x] != 0, ra, (unsigned long long)L[x], 0ull, lsum, nullptr);
+        }
       }
       if (ok && h != g - base) atomicAdd(a.size + base + h, 1u);
     }
-    // the segment's latest arrival, once per wave
+    // the segment's latest arrival, once per work-group
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) {
       const unsigned long long o = (unsigned long long)__shfl_xor((long long)mts, m, 64);
       mts = o > mts ? o : mts;
     }
     const bool any_w = __ballot(any) != 0;
-    if (lane == 0 && any_w) atomicMax(a.max_ts + r, mts);
+    if (lane == 0) sm.red[wave] = any_w ? mts + 1 : 0;  // 0: no valid request
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      unsigned long long m = 0;
+      for (int w = 0; w < kThreads / 64; ++w) m = sm.red[w] > m ? sm.red[w] : m;
+      if (m) atomicMax(a.max_ts + r, m - 1);
+    }
+    if (LDS) {
+      for (int k = threadIdx.x; k < A * 3 * kLenBins; k += kThreads) {
+        const uint32_t c = sm.lh[k];
+        if (c) {
+          atomicAdd(lh + int64_t(r) * A * 3 * kLenBins + k, (unsigned long long)c);
+          sm.lh[k] = 0;
+        }
+      }
+      for (int k = threadIdx.x; k < A * 3; k += kThreads) {
+        const unsigned long long c = sm.ls[k];
+        if (c) {
+          atomicAdd(lsum + int64_t(r) * A * 3 + k, c);
+          sm.ls[k] = 0;
+        }
+      }
+    }
   }
   if (code) raise_err(a.err, code);
 }
@@ -820,8 +863,10 @@ hipError_t launch_workload(const fs_trace *t, int64_t minute_us, const fs_wstats
       hipLaunchKernelGGL(k_ws_records_hash, dim3(uint32_t((N + a.chunk - 1) / a.chunk)),
                          dim3(kRecThreads), lds, s, a);
       a.chunk = chunk;
+    } else if (t->n_apps <= kLdsApps) {
+      hipLaunchKernelGGL(k_ws_records<true>, chunks, dim3(kThreads), 0, s, a);
     } else {
-      hipLaunchKernelGGL(k_ws_records, chunks, dim3(kThreads), 0, s, a);
+      hipLaunchKernelGGL(k_ws_records<false>, chunks, dim3(kThreads), 0, s, a);
     }
     if (t->n_apps <= kLdsApps)
       hipLaunchKernelGGL(k_ws_graph<true>, chunks, dim3(kThreads), 0, s, a);

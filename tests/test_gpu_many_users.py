@@ -78,3 +78,27 @@ def test_workload_many_keys(sizes, U, A):
     for k, v in got.items():
         w = getattr(want, k)
         assert (v.reshape(w.shape) == w).all(), k
+
+
+@pytest.mark.parametrize("U,A", [((1 << 26) + 1, 64), ((1 << 32) // 33, 33), (1 << 27, 32)])
+def test_workload_more_keys_than_32_bits(U, A):
+    """(replica, user, app) keys just below and beyond 2^32 (64 GiB of workspace; the histograms
+    are those of the same requests with the users numbered densely)."""
+    rng = np.random.default_rng(A)
+    say("workload wide keys", U, A)
+    tr = _trace(rng, 30_000, U, A)
+    ids, dense = np.unique(tr.user, return_inverse=True)
+    d = tg.Trace(1, ids.size, A, tr.rep_off, tr.ts_us, dense.astype(np.int32), tr.app, tr.call, tr.head, tr.prev,
+                 tr.len_in, tr.len_sys, tr.len_out)
+    want = oracle.workload_stats(d, 60_000_000)
+    got = fs.fs_workload_stats(fs.DeviceTrace(tr), 60_000_000, per_app=False)
+    at = torch.as_tensor(ids.astype(np.int64)).cuda()
+    for k in ("user_req", "user_tok"):
+        v = getattr(got, k)
+        assert (v[0, at].cpu().numpy() == getattr(want, k)[0]).all(), k
+        assert int(v.sum()) == int(getattr(want, k).sum()), k
+    for k in ("minutes", "rate_hist", "len_hist", "len_sum", "size_hist", "graph"):
+        w = getattr(want, k)
+        assert (getattr(got, k).cpu().numpy().reshape(w.shape) == w).all(), k
+    del got, v
+    torch.cuda.empty_cache()
