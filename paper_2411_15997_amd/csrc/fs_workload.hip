@@ -873,8 +873,9 @@ hipError_t launch_workload(const fs_trace *t, int64_t minute_us, const fs_wstats
     else
       hipLaunchKernelGGL(k_ws_graph<false>, chunks, dim3(kThreads), 0, s, a);
   }
-  const int64_t spans = int64_t(t->n_replicas) * ((t->n_users + kUserSpan - 1) / kUserSpan);
-  if (t->n_apps <= kRateApps && spans <= (int64_t(1) << 30)) {
+  // (a launch has fewer than 2^32 threads: 2^31 users in all take one work-group too many)
+  const int64_t spans = t->n_replicas * ((int64_t(t->n_users) + kUserSpan - 1) / kUserSpan);
+  if (t->n_apps <= kRateApps && spans * kUserThreads < (int64_t(1) << 32)) {
     const size_t lds = users_lds_bytes(t->n_apps);
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_ws_users_lds),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));

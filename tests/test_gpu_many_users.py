@@ -102,3 +102,27 @@ def test_workload_more_keys_than_32_bits(U, A):
         assert (getattr(got, k).cpu().numpy().reshape(w.shape) == w).all(), k
     del got, v
     torch.cuda.empty_cache()
+
+
+def test_workload_two_to_the_31_users():
+    """2 x 2^30 users, the most a trace may have (64 GiB of workspace and outputs)."""
+    U, n = 1 << 30, 3000
+    rng = np.random.default_rng(31)
+    say("workload 2^31 users")
+    tr = tg.concat([_trace(rng, n, U, 1) for _ in range(2)])
+    got = fs.fs_workload_stats(fs.DeviceTrace(tr), 60_000_000, per_app=False)
+    for r in range(2):
+        m = slice(r * n, (r + 1) * n)
+        ids, dense = np.unique(tr.user[m], return_inverse=True)
+        d = tg.Trace(1, ids.size, 1, np.array([0, n], np.int64), tr.ts_us[m], dense.astype(np.int32), tr.app[m],
+                     tr.call[m], tr.head[m], tr.prev[m], tr.len_in[m], tr.len_sys[m], tr.len_out[m])
+        want = oracle.workload_stats(d, 60_000_000)
+        at = torch.as_tensor(ids.astype(np.int64)).cuda()
+        for k in ("user_req", "user_tok"):
+            v = getattr(got, k)[r]
+            assert (v[at].cpu().numpy() == getattr(want, k)[0]).all(), (r, k)
+            assert int(v.sum()) == int(getattr(want, k).sum()), (r, k)
+        for k in ("minutes", "rate_hist", "len_hist", "len_sum", "size_hist", "graph"):
+            assert (getattr(got, k)[r].cpu().numpy() == getattr(want, k)[0]).all(), (r, k)
+    del got, v
+    torch.cuda.empty_cache()
