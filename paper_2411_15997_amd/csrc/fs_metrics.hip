@@ -522,9 +522,9 @@ struct UserSums {
   U128 s1 = {0, 0}, s2 = {0, 0};
   unsigned long long cnt[3] = {0, 0, 0};  // users with a request, fully served, delayed
 };
-__device__ inline UserSums user_sums(const MArgs &a, int32_t r, int32_t k0, int32_t k1) {
+__device__ inline UserSums user_sums(const MArgs &a, int32_t r, int64_t k0, int64_t k1) {
   UserSums u;
-  for (int32_t k = k0 + threadIdx.x; k < k1; k += blockDim.x) {
+  for (int64_t k = k0 + threadIdx.x; k < k1; k += blockDim.x) {  // (k1 may be 2^31 - 1)
     const int64_t uk = int64_t(r) * a.t.U + k;
     const uint32_t f = a.uflags[uk];
     const unsigned long long x = a.charged[uk];
@@ -563,8 +563,8 @@ __device__ inline void block_sums(const UserSums &u, SumsLds &sm) {
 __global__ void __launch_bounds__(256) k_m_user_parts(MArgs a) {
   __shared__ SumsLds sm;
   const int32_t r = blockIdx.x / a.parts, p = blockIdx.x % a.parts;
-  const int32_t per = (a.t.U + a.parts - 1) / a.parts;
-  const int32_t k0 = p * per, k1 = k0 + per < a.t.U ? k0 + per : a.t.U;
+  const int64_t U = a.t.U, per = (U + a.parts - 1) / a.parts;
+  const int64_t k0 = p * per, k1 = k0 + per < U ? k0 + per : U;
   block_sums(user_sums(a, r, k0, k1), sm);
   if (threadIdx.x == 0) {
     unsigned long long *const o = a.part + int64_t(blockIdx.x) * 8;

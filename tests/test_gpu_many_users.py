@@ -126,3 +126,36 @@ def test_workload_two_to_the_31_users():
             assert (getattr(got, k)[r].cpu().numpy() == getattr(want, k)[0]).all(), (r, k)
     del got, v
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n", [900, 5000])
+def test_metrics_two_to_the_31_users(n):
+    """One replica of 2^31 - 1 users, the last of them with requests: the finish pass in one
+    work-group and in parts (40 GiB; the metrics are those of the users numbered densely)."""
+    U = (1 << 31) - 1
+    rng = np.random.default_rng(n)
+    say("metrics 2^31 users", n)
+    tr = _trace(rng, n, U - 600, 2)
+    tr.n_users = U
+    tr.user = np.where(tr.user % 3 == 0, U - 1 - tr.user % 599, tr.user).astype(np.int32)
+    ids, dense = np.unique(tr.user, return_inverse=True)
+    step = 50_000
+    cost = rng.integers(0, 10 ** 6, n).astype(np.int64)
+    status = rng.choice(np.array([0, 0, 0, 1, 2, 3], np.int8), n)
+    astep = np.where(status == 0, tr.ts_us // step + rng.integers(0, 3, n), -1).astype(np.int32)
+    gap = np.array([123], np.int64)
+    dt = fs.DeviceTrace(tr)
+    out = fs.Outputs(dt, parity=False)
+    out.status[:n].copy_(torch.as_tensor(status))
+    out.admit_step[:n].copy_(torch.as_tensor(astep))
+    out.max_gap.copy_(torch.as_tensor(gap))
+    m = fs.fs_fairness_metrics(dt, torch.as_tensor(cost).cuda(), out, fs.make_engine(step, 1000, 1000)).host()
+    d = tg.Trace(1, ids.size, 2, tr.rep_off, tr.ts_us, dense.astype(np.int32), tr.app, tr.call, tr.head, tr.prev,
+                 tr.len_in, tr.len_sys, tr.len_out)
+    o = oracle.fairness_metrics(d, cost, status, astep, gap, step, 0)
+    for k in ("throttled", "aborted_midway", "wasted_tokens"):
+        assert (m[k] == getattr(o, k)).all(), k
+    for k in ("jain", "svc_req_pct", "svc_int_pct", "served_users_pct", "delayed_users_pct"):
+        np.testing.assert_allclose(m[k], getattr(o, k), rtol=1e-14, atol=0, err_msg=k)
+    del dt, out
+    torch.cuda.empty_cache()
