@@ -111,7 +111,8 @@ __device__ inline bool cost_ok(int64_t c) { return c >= 0 && c < kValueLimit; }
 // memory once.  Per-replica counts are reduced over the work-group.
 constexpr int kChunk = 8192;      // at most
 constexpr int kChunkLeast = 1024;
-constexpr int kLdsUsers = 4096;
+constexpr int kLdsUsers = 4096;  // beyond, the hash tables below (at 4,096 users the indexed ones take
+                                 // 146 us against 304 for 1M requests, 426 against 486 for 10M)
 
 // Sums three per-thread counts over the work-group (NW waves) and adds them to the
 // replica's counters c0, c1, c2 (c < 0: unused).
@@ -662,9 +663,16 @@ hipError_t launch_metrics(const fs_trace *t, const int64_t *cost, const fs_outpu
     parts = std::min<int64_t>(parts, std::max<int64_t>(1024 / t->n_replicas, 1));
     if (parts > 1 && size_t(t->n_replicas) * size_t(parts) * 64 <= size_t(N) * 4) a.parts = int32_t(parts);
   }
-  // Chunks of kChunk records, less when they would leave the chip idle (four a CU); the
-  // tables are cleared and added once per chunk.
-  a.chunk = int32_t(std::min<int64_t>(kChunk, std::max<int64_t>(kChunkLeast, (N / 1024 + 255) / 256 * 256)));
+  // Chunks of kChunk records, less when they would leave the chip idle (four a CU), but at
+  // most 256 of one replica: its counters are one line that every chunk of it adds to.  One
+  // replica of 1M requests in 1,024, 512, 256 and 128 chunks: 173, 115, 108 and 149 us with
+  // 1,024 users, 242, 167, 146 and 170 us with 4,096; 64 replicas of 20,000 requests in 1,280,
+  // 640, 320 and 192 chunks: 71, 84, 107 and 162 us.
+  int64_t most_n = 0;
+  for (int32_t r = 0; r < t->n_replicas; ++r)
+    most_n = std::max<int64_t>(most_n, t->rep_off_h[r + 1] - t->rep_off_h[r]);
+  const int64_t per = std::max<int64_t>(std::max<int64_t>(N / 1024, most_n / 256), kChunkLeast);
+  a.chunk = int32_t(std::min<int64_t>(kChunk, (per + 255) / 256 * 256));
   if (N > 0) {
     const int64_t chunks = (N + a.chunk - 1) / a.chunk;
     if (t->n_users <= kLdsUsers) {

@@ -159,3 +159,12 @@ def test_metrics_two_to_the_31_users(n):
         np.testing.assert_allclose(m[k], getattr(o, k), rtol=1e-14, atol=0, err_msg=k)
     del dt, out
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("links", [True, False])
+@pytest.mark.parametrize("sizes,U", [([262_145], 4096), ([524_289, 1, 0, 700], 100), ([5] * 40 + [300_001], 1024)])
+def test_metrics_chunks(sizes, U, links):
+    """Directly indexed users: chunks that follow from the largest replica, not from the total."""
+    rng = np.random.default_rng(U + links)
+    say("metrics chunks", sizes[-1], U, links)
+    _metrics(tg.concat([_trace(rng, n, U, 3, links) for n in sizes]), rng)
