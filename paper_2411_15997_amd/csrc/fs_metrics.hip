@@ -317,6 +317,49 @@ struct HashLds {
 
 __device__ inline uint32_t hash_slot(uint32_t key) { return (key * 2654435761u) >> (32 - kHashBits); }
 
+// Replicas of few requests: with the counts reduced over the work-group segment after segment,
+// its barriers (and idle waves) take longer than the records, so there each wave takes
+// segments of its own and adds their counts itself.  20,000 replicas of 50 requests: 1,163 us by
+// the work-group, 663 by waves; 2,000 of 500: 202 and 167; 1,000 of 1,000: 148 and 148; 64 of
+// 1,000: 88 and 100; 500 of 2,000: 133 and 170.
+constexpr int kWaveSegment = 512;  // requests a replica on average, below which waves take them (and
+                                   // no replica has four times as many)
+
+// Adds three per-thread counts and the costs' halves, summed over the wave, to the counters.
+__device__ inline void wave_counts(uint32_t x0, uint32_t x1, uint32_t x2, unsigned long long *cr, int c0,
+                                   int c1, int c2, int c0b, unsigned long long lo, unsigned long long hi) {
+  const unsigned long long t =
+      wave_sum(uint64_t(x0) | (uint64_t(x1) << 21) | (uint64_t(x2) << 42));  // (at most a chunk's records)
+  const unsigned long long tl = wave_sum(lo), th = wave_sum(hi);
+  if ((threadIdx.x & 63) != 0) return;
+  const unsigned long long m = (uint64_t(1) << 21) - 1;
+  if (t & m) atomicAdd(cr + c0, t & m);
+  if (c0b >= 0 && (t & m)) atomicAdd(cr + c0b, t & m);
+  if ((t >> 21) & m) atomicAdd(cr + c1, (t >> 21) & m);
+  if (c2 >= 0 && ((t >> 42) & m)) atomicAdd(cr + c2, (t >> 42) & m);
+  if (tl) atomicAdd(cr + C_COST_LO, tl);
+  if (th) atomicAdd(cr + C_COST_HI, th);
+}
+
+// The replica segments of a work-group's chunk [c0, c1): take(r, s0, s1) for each, by the whole
+// work-group one after the other, or (WAVES) by each wave for every kHashWaves-th.
+template <bool WAVES, class F>
+__device__ __forceinline__ void for_segments(const DevTrace &t, int64_t c0, int64_t c1, F take) {
+  int32_t r = replica_of(t.rep_off, t.R, c0);
+  if (WAVES) {
+    for (r += threadIdx.x >> 6; r < t.R && t.rep_off[r] < c1; r += kHashWaves) {
+      const int64_t b = t.rep_off[r], e = t.rep_off[r + 1];
+      if (e > c0 && e > b) take(r, b > c0 ? b : c0, e < c1 ? e : c1);
+    }
+    return;
+  }
+  for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
+    while (t.rep_off[r + 1] <= s0) ++r;  // (empty replicas)
+    take(r, s0, t.rep_off[r + 1] < c1 ? t.rep_off[r + 1] : c1);
+  }
+}
+
+template <bool WAVES>
 __global__ void __launch_bounds__(kHashThreads) k_m_records_hash(MArgs a) {
   extern __shared__ __align__(16) unsigned char m_smem[];
   HashLds &sm = *reinterpret_cast<HashLds *>(m_smem);
@@ -329,21 +372,20 @@ __global__ void __launch_bounds__(kHashThreads) k_m_records_hash(MArgs a) {
   __syncthreads();
   const int64_t c0 = blockIdx.x * int64_t(a.chunk);
   const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
-  int32_t r = replica_of(t.rep_off, t.R, c0);
+  constexpr int kT = WAVES ? 64 : kHashThreads;  // threads a segment is taken by
+  const int tid = WAVES ? threadIdx.x & 63 : threadIdx.x;
   int32_t code = 0;
-  for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
-    while (t.rep_off[r + 1] <= s0) ++r;  // (empty replicas)
+  for_segments<WAVES>(t, c0, c1, [&](int32_t r, int64_t s0, int64_t s1) {
     const int64_t base = t.rep_off[r];
-    const int64_t s1 = t.rep_off[r + 1] < c1 ? t.rep_off[r + 1] : c1;
     uint32_t n_adm = 0, n_thr = 0, n_int = 0;
     unsigned long long c_lo = 0, c_hi = 0;
-    for (int64_t g0 = s0 + threadIdx.x; g0 < s1; g0 += kRecBatch * kHashThreads) {
+    for (int64_t g0 = s0 + tid; g0 < s1; g0 += kRecBatch * kT) {
       int32_t uk[kRecBatch], ap[kRecBatch], cl[kRecBatch], hd[kRecBatch], as[kRecBatch];
       int8_t st[kRecBatch];
       int64_t ts[kRecBatch], cs[kRecBatch];
 #pragma unroll
       for (int j = 0; j < kRecBatch; ++j) {
-        const int64_t g = g0 + j * kHashThreads;
+        const int64_t g = g0 + j * kT;
         const bool v = g < s1;
         uk[j] = v ? t.user[g] : 0;
         ap[j] = v ? t.app[g] : 0;
@@ -356,7 +398,7 @@ __global__ void __launch_bounds__(kHashThreads) k_m_records_hash(MArgs a) {
       }
 #pragma unroll
       for (int j = 0; j < kRecBatch; ++j) {
-        const int64_t g = g0 + j * kHashThreads;
+        const int64_t g = g0 + j * kT;
         if (g >= s1) continue;
         const int64_t i = g - base;
         bool ok = uk[j] >= 0 && uk[j] < t.U && ap[j] >= 0 && ap[j] < t.A;
@@ -404,12 +446,17 @@ __global__ void __launch_bounds__(kHashThreads) k_m_records_hash(MArgs a) {
       }
     }
     unsigned long long *const cr = a.counters + int64_t(r) * C_NUM;
+    if (WAVES) {
+      wave_counts(n_adm, n_thr, n_int, cr, C_ADMITTED, C_THROTTLED, C_INTERACTIONS, t.call ? -1 : int(C_FULL),
+                  c_lo, c_hi);
+      return;
+    }
     block_count3<kHashWaves>(n_adm, n_thr, n_int, cr, C_ADMITTED, C_THROTTLED, C_INTERACTIONS, sm.red,
                              t.call ? -1 : int(C_FULL));
     __syncthreads();
     block_cost2<kHashWaves>(c_lo, c_hi, cr, sm.red);
     __syncthreads();
-  }
+  });
   __syncthreads();
   for (int k = threadIdx.x; k < kHashSlots; k += kHashThreads) {
     const uint32_t key = sm.key[k];
@@ -424,6 +471,7 @@ __global__ void __launch_bounds__(kHashThreads) k_m_records_hash(MArgs a) {
 // Pass 2 with many users: a fully served interaction sets its user's flag once per
 // work-group (a direct-mapped table of the users already seen) and only when the flag is
 // not yet visible.
+template <bool WAVES>
 __global__ void __launch_bounds__(kHashThreads) k_m_interactions_hash(MArgs a) {
   __shared__ uint32_t s_seen[kHashSlots];
   __shared__ unsigned long long s_red[2][kHashWaves];
@@ -432,18 +480,17 @@ __global__ void __launch_bounds__(kHashThreads) k_m_interactions_hash(MArgs a) {
   __syncthreads();
   const int64_t c0 = blockIdx.x * int64_t(a.chunk);
   const int64_t c1 = c0 + a.chunk < t.N ? c0 + a.chunk : t.N;
-  int32_t r = replica_of(t.rep_off, t.R, c0);
-  for (int64_t s0 = c0; s0 < c1; s0 = t.rep_off[r + 1], ++r) {
-    while (t.rep_off[r + 1] <= s0) ++r;
-    const int64_t s1 = t.rep_off[r + 1] < c1 ? t.rep_off[r + 1] : c1;
+  constexpr int kT = WAVES ? 64 : kHashThreads;
+  const int tid = WAVES ? threadIdx.x & 63 : threadIdx.x;
+  for_segments<WAVES>(t, c0, c1, [&](int32_t r, int64_t s0, int64_t s1) {
     uint32_t n_full = 0, n_ab = 0;
-    for (int64_t g0 = s0 + threadIdx.x; g0 < s1; g0 += kRecBatch * kHashThreads) {
+    for (int64_t g0 = s0 + tid; g0 < s1; g0 += kRecBatch * kT) {
       int32_t uk[kRecBatch];
       uint32_t f[kRecBatch];
       bool ok[kRecBatch];
 #pragma unroll
       for (int j = 0; j < kRecBatch; ++j) {
-        const int64_t g = g0 + j * kHashThreads;
+        const int64_t g = g0 + j * kT;
         ok[j] = g < s1 && first_call(t, g);
         uk[j] = g < s1 ? t.user[g] : -1;
         f[j] = g < s1 ? (later_iflags(a, g) | own_iflag(a.status[g])) : 0u;
@@ -463,10 +510,14 @@ __global__ void __launch_bounds__(kHashThreads) k_m_interactions_hash(MArgs a) {
           atomicOr(a.uflags + key, uint32_t(U_FULL));
       }
     }
-    block_count3<kHashWaves>(n_full, n_ab, 0, a.counters + int64_t(r) * C_NUM, C_FULL, C_ABORTED, -1,
-                             s_red);
+    unsigned long long *const cr = a.counters + int64_t(r) * C_NUM;
+    if (WAVES) {
+      wave_counts(n_full, n_ab, 0, cr, C_FULL, C_ABORTED, -1, -1, 0, 0);
+      return;
+    }
+    block_count3<kHashWaves>(n_full, n_ab, 0, cr, C_FULL, C_ABORTED, -1, s_red);
     __syncthreads();
-  }
+  });
 }
 
 // Pass 3: per admitted record of an aborted interaction -- wasted tokens.  Chunked like
@@ -680,7 +731,10 @@ hipError_t launch_metrics(const fs_trace *t, const int64_t *cost, const fs_outpu
       if (t->call)  // (without links the records pass counts the fully served interactions)
         hipLaunchKernelGGL(k_m_interactions_lds, dim3(chunks), dim3(256), size_t(t->n_users), s, a);
     } else {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k_m_records_hash),
+      const bool waves = N / t->n_replicas < kWaveSegment && most_n < 4 * kWaveSegment;
+      const auto records = waves ? k_m_records_hash<true> : k_m_records_hash<false>;
+      const auto interactions = waves ? k_m_interactions_hash<true> : k_m_interactions_hash<false>;
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(records),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(sizeof(HashLds)));
       const int32_t chunk = a.chunk;
       // a whole number of work-groups a CU, each of at most kHashChunk records
@@ -688,9 +742,9 @@ hipError_t launch_metrics(const fs_trace *t, const int64_t *cost, const fs_outpu
       const int64_t per = (N + rounds * 256 - 1) / (rounds * 256);
       a.chunk = int32_t(std::max<int64_t>((per + 255) / 256 * 256, 2048));
       const int64_t groups = (N + a.chunk - 1) / a.chunk;
-      hipLaunchKernelGGL(k_m_records_hash, dim3(groups), dim3(kHashThreads), sizeof(HashLds), s, a);
+      hipLaunchKernelGGL(records, dim3(groups), dim3(kHashThreads), sizeof(HashLds), s, a);
       if (t->call)
-        hipLaunchKernelGGL(k_m_interactions_hash, dim3(groups), dim3(kHashThreads), 0, s, a);
+        hipLaunchKernelGGL(interactions, dim3(groups), dim3(kHashThreads), 0, s, a);
       a.chunk = chunk;
     }
     hipLaunchKernelGGL(k_m_wasted, dim3(chunks), dim3(256), 0, s, a);

@@ -168,3 +168,14 @@ def test_metrics_chunks(sizes, U, links):
     rng = np.random.default_rng(U + links)
     say("metrics chunks", sizes[-1], U, links)
     _metrics(tg.concat([_trace(rng, n, U, 3, links) for n in sizes]), rng)
+
+
+@pytest.mark.parametrize("links", [True, False])
+@pytest.mark.parametrize("sizes", [[37] * 300, [511, 0, 0, 513, 1, 2047] * 3, [40, 0] * 60 + [2048], [300] * 70])
+def test_metrics_short_replicas(sizes, links):
+    """Replicas of few requests and many users (taken by single waves), on both sides of the
+    sizes where the whole work-group takes a replica; more replicas in a chunk than waves, and
+    replicas cut by the end of a chunk."""
+    rng = np.random.default_rng(len(sizes) + links)
+    say("metrics short replicas", len(sizes), links)
+    _metrics(tg.concat([_trace(rng, n, 4100, 3, links) for n in sizes]), rng)
