@@ -361,18 +361,15 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     return x;
   };
   // Data of an arrived record read from the inputs (when it is no longer cached).
-  // (false: it does not fit a packed request)
-  auto load_rec = [&](int32_t i, int32_t &sc, uint32_t &lo, uint32_t &hi) -> bool {
+  auto load_rec = [&](int32_t i, int32_t &sc, uint32_t &lo, uint32_t &hi) {
     const int64_t g = base + i;
     const int32_t *len_sys = KARG(t.len_sys);
     const int32_t tok =
         KARG(t.len_in)[g] + KARG(t.len_out)[g] + (len_sys ? len_sys[g] : 0);
-    const int64_t cst = KARG(cost)[g];
-    const uint64_t pk = (uint64_t(cst) << 24) | uint32_t(tok);
+    const uint64_t pk = (uint64_t(KARG(cost)[g]) << 24) | uint32_t(tok);
     sc = uni(STATE(const int32_t, succ)[base + i]);
     lo = uint32_t(uni(int32_t(uint32_t(pk))));
     hi = uint32_t(uni(int32_t(uint32_t(pk >> 32))));
-    return fits_packed(cst, tok);
   };
 
   // ---- admissions waiting to be written: lane i holds the i-th of nd
@@ -798,37 +795,44 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
     return true;
   };
 
-  // ---- rebuild the queue left by a previous call: arrived records still undecided
+  // ---- rebuild the queue left by a previous call: arrived records still undecided.  The
+  // fields of 64 of them are loaded together (one after the other, each with its own dependent
+  // loads, took XXXX).
   for (int32_t b0 = low; b0 < nxt && !overflow; b0 += 64) {
     const int8_t *const fate = STATE(const int8_t, fate) + base;
     const int32_t i = b0 + lane;
     const bool q = i < nxt && ld_fresh(fate + i) == -1;
     uint64_t m = bal(q);
+    if (!m) continue;
+    const int64_t g = base + (q ? i : b0);
+    const int32_t *const len_sys = KARG(t.len_sys);
+    const int32_t *const callp = KARG(t.call);
+    const int32_t ku = KARG(t.user)[g];
+    const int32_t tok = KARG(t.len_in)[g] + KARG(t.len_out)[g] + (len_sys ? len_sys[g] : 0);
+    const int64_t cst = KARG(cost)[g];
+    const int32_t call = callp ? callp[g] : 0;
+    const int32_t pv = callp && !fcfs ? KARG(t.prev)[g] : -1;
+    const int32_t scv = callp ? STATE(const int32_t, succ)[g] : -1;
+    const uint32_t sbv = STATE(const uint32_t, seg_start)[int64_t(r) * U + ku];
+    const int64_t uv = ulds ? u_lds[ku] : ld_fresh(u_all + ku);
+    const uint64_t pk = (uint64_t(cst) << 24) | uint32_t(tok);
+    const uint64_t padmm = fcfs ? 0 : bal(q && call > 0 && ld_fresh(fate + (pv >= 0 ? pv : 0)) == 0);
+    const uint64_t laterm = bal(call > 0);
+    if (bal(q && !fits_packed(cst, tok))) overflow = true;
     while (m && !overflow) {
       const int l = ff1(m);
       m &= m - 1;
-      const int32_t rec = b0 + l;
-      const int64_t g = base + rec;
-      const int32_t k = uni(KARG(t.user)[g]);
-      const int32_t *const callp = KARG(t.call);
-      const int32_t call = callp ? uni(callp[g]) : 0;
-      int32_t sc;
-      uint32_t lo, hi;
-      const bool big = !load_rec(rec, sc, lo, hi);
-      const bool padm = !fcfs && call > 0 && ld_fresh(fate + uni(KARG(t.prev)[g])) == 0;
+      const int32_t rec = b0 + l, k = rdl(ku, l), sc = rdl(scv, l);
+      const uint32_t lo = rdlu(uint32_t(pk), l), hi = rdlu(uint32_t(pk >> 32), l);
+      const bool padm = (padmm >> l) & 1;
       const uint64_t fm = bal(xu == k);
-      if (big || (fm == 0 && nX == kSlots) || (padm && pocc == ~uint64_t(0))) {
+      if ((fm == 0 && nX == kSlots) || (padm && pocc == ~uint64_t(0))) {
         overflow = true;  // nothing in the state buffer has changed yet
         break;
       }
-      int32_t x = ff1(fm);
-      if (fm == 0) {
-        const int64_t uk = uni64(ulds ? u_lds[k] : ld_fresh(u_all + k));
-        const uint32_t sb = uint32_t(uni(int32_t(STATE(const uint32_t, seg_start)[int64_t(r) * U + k])));
-        x = join(k, uk, sb);
-      }
+      const int32_t x = fm ? ff1(fm) : join(k, rdl64(uv, l), rdlu(sbv, l));
       if (lane == x) ++xq;
-      if (call == 0 || fcfs)
+      if (!((laterm >> l) & 1) || fcfs)
         fifo_push(x, rec, sc, lo, hi);
       else if (padm)
         ready_add(x, rec, sc, lo, hi);
