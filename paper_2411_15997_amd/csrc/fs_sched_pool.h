@@ -121,6 +121,18 @@ constexpr int kPoolRoom = 28, kPoolShare = 6;
 // kNearLeast calls are: a ranking costs about 55 clocks a call and a step admits a handful.
 constexpr int kNearMin = 20, kNearLeast = 8, kNearRank = 16;
 
+// A queue that the slot pass serves faster is handed over to it: kDeep spilled calls or more and
+// fewer than kSlowNum / kSlowDen admissions a batch over the last kRateBatches (chains whose next
+// calls have arrived end most batches after one or two calls, and each batch is ranked anew).
+// 64 replicas of 20,000 requests at 0.8 of the capacity take 16.0 ms in the slot pass, 21.1 in
+// the pool and 16.8 with this rule; at 0.6 and never throttled 73.2, 87.0 and 74.7.  64 of
+// 100,000 requests: 16 traces of one kind 75 to 80 ms in the slot pass, up to 88.3 in the pool
+// and 82.4 here, 12 of another 74 to 79, 55 to 89 and 55 to 81.  A rate of 2 (or a look every
+// 128 batches) also hands over queues that the pool serves faster (64.9 -> 74 ms), a rate of 5/3
+// leaves some that it serves slower (82.4 for 78.8); 256 spilled calls instead of 64 16.8 -> 17.1.
+constexpr int kDeep = 64, kSlowNum = 9, kSlowDen = 5, kRateBatches = 512;
+constexpr int32_t kOutDeep = 3;  // rs->overflow of a replica handed over for its queue
+
 // A slot's record: the counter after the user's pooled calls; the number of pooled calls, of
 // the ready ones among them (kRdyOne each) and the user's window lane plus one (kWinOne
 // each), all at most 64; the number of spilled calls (as many as the replica has records).
@@ -1040,6 +1052,10 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
   // arrivals at a time, or for another batch of the step.  (One loop, so that the values
   // it carries have one place and are not copied between loops.)
   int64_t budget = 0;
+  // batches that ended early since the last look at their rate (the others end a step each),
+  // the step and the admissions then
+  int32_t cuts = 0, s_look = s, seq_look = seq;
+  bool deep = false;
   bool admit = false;  // the step's arrivals are done
   bool moved = false;  // the step has admitted
   int32_t lim = 64;    // arrivals taken at once
@@ -1049,6 +1065,19 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
         const int32_t old = wbase;
         wbase = nxt;
         load_window(old);
+        const int32_t batches = cuts + (s - s_look);
+        if (LINKS && batches >= kRateBatches) {
+          // (the slot pass rebuilds the queue first: not for fewer steps than queued calls)
+          deep = sp_total >= kDeep && int64_t(seq - seq_look) * kSlowDen < int64_t(batches) * kSlowNum &&
+                 s_end - s >= int64_t(sp_total);
+          if (deep) {
+            overflow = true;
+            break;
+          }
+          cuts = 0;
+          s_look = s;
+          seq_look = seq;
+        }
       }
       if (int64_t(s) >= s_end) break;
       const int j = nxt - wbase;
@@ -1206,6 +1235,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
           fetch_rec(c_sc, s2, lo2, hi2);
           ready_insert(c_x, c_sc, s2, lo2, hi2);
         }
+        if (LINKS) ++cuts;
         if (sp_total > 0 && uni(int32_t(s_slot[c_x].num & kNumMask)) == 0) spill_refill(c_x);
         continue;
       }
@@ -1273,7 +1303,7 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
     rs->low = low;
     rs->last_exit = last_exit;
     rs->done = drained ? 1 : 0;
-    rs->overflow = overflow ? 1 : 0;
+    rs->overflow = deep ? kOutDeep : overflow ? 1 : 0;
     rs->mid = 0;
     rs->mid_budget = 0;
     rs->s_end = s_end;

@@ -146,3 +146,21 @@ def test_pool_many_spilled_calls_of_one_user(queued, sliced):
     for k, want in (("admit_seq", seq), ("admit_step", step), ("counter_after", after)):
         bad = np.nonzero(h[k] != want)[0]
         assert bad.size == 0, (k, bad.size, bad[:5], h[k][bad[:5]], want[bad[:5]])
+
+
+@pytest.mark.parametrize("users,cap", [(20, 12), (45, 20), (90, 14)])
+def test_pool_deep_queues_of_chains(users, cap):
+    """Overloads long enough that a replica's queue of chained calls is handed to the slot pass,
+    and quiet stretches in which the pool takes it back; with more users than lanes as well."""
+    rng = np.random.default_rng(users)
+    say("pool deep chains", users, cap)
+    trs = []
+    for _ in range(3):
+        tr = random_trace(rng, 9000, users, 2, 100, multi=True, max_tok=6)
+        tr.ts_us = np.sort(np.concatenate([b * 600_000 + rng.integers(0, 40_000, 3000) for b in range(3)])).astype(np.int64)
+        trs.append(tr)
+    tr = tg.concat(trs)
+    cost = rng.integers(0, 900, tr.n).astype(np.int64)
+    reason = rng.integers(0, 3, tr.n).astype(np.uint8)
+    for theta in (10 ** 9, 3000):
+        _check(tr, cost, reason, 100, cap, theta, 2500)
