@@ -123,7 +123,7 @@ __device__ inline void block_count3(uint32_t x0, uint32_t x1, uint32_t x2,
                                     unsigned long long (*s_red)[NW], int c0b = -1) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const unsigned long long packed =
-      uint64_t(x0) | (uint64_t(x1) << 21) | (uint64_t(x2) << 42);  // each at most kChunk
+      uint64_t(x0) | (uint64_t(x1) << 21) | (uint64_t(x2) << 42);  // each at most a chunk's records
   const unsigned long long tw = wave_sum(packed);
   if (lane == 0) s_red[0][wave] = tw;
   __syncthreads();
@@ -139,7 +139,7 @@ __device__ inline void block_count3(uint32_t x0, uint32_t x1, uint32_t x2,
 }
 
 // Adds the work-group's sums of the admitted costs' low and high halves to the
-// replica's counters (each block sum is below 2^45).
+// replica's counters (each block sum is below 2^48: a chunk has fewer than 2^16 records).
 template <int NW = 4>
 __device__ inline void block_cost2(unsigned long long lo, unsigned long long hi,
                                    unsigned long long *cr, unsigned long long (*s_red)[NW]) {
@@ -306,6 +306,7 @@ constexpr int kHashWaves = kHashThreads / 64;
 constexpr int kHashBits = 13;
 constexpr int kHashSlots = 1 << kHashBits;
 constexpr int kHashChunk = 40960;  // records of a work-group, at most
+static_assert(kChunk < (1 << 16) && kHashChunk < (1 << 16), "packed counts and the block sums of the costs");
 constexpr int kHashProbes = 8;
 constexpr uint32_t kHashEmpty = 0xffffffffu;  // (a key is below R * U <= 2^31)
 

@@ -25,12 +25,12 @@
 // memory or matrix unit is near its rate), so the work per step is what is kept small.  One
 // call per lane replaced one user per lane with sequential admissions (about 1,300 clocks
 // each: an argmin, the chosen user's next call and its new key in a dependent chain), which
-// remains in fs_sched_onchip.hip for the policy flags, the literal engine and the replicas that
-// outgrow the pool (more than 64 users and ready calls at once).  Kernel and set-up, before
-// and after: one replica of 300,000 requests, 100,000 users and 17 admissions a step 204 -> 59 ms;
-// 1,024 replicas of 20,000 requests without interactions 12.8 -> 9.0 ms; 64 replicas of
-// 100,000 requests 74.7 -> 60.9 ms (54 to 65 ms over most seeds; 73 to 82 ms where a replica
-// has thousands of calls queued for most of its steps, against 75 to 77).
+// remains in fs_sched_onchip.hip for the policy flags, the literal engine, the replicas that
+// outgrow the pool (more than 64 users and ready calls at once) and deep queues of chained calls
+// (kDeep).  Kernel and set-up, before and after: one replica of 300,000 requests, 100,000 users
+// and 17 admissions a step 204 -> 59 ms; 1,024 replicas of 20,000 requests without interactions
+// 12.8 -> 8.9 ms; 64 replicas of 100,000 requests, 12 traces, 74-79 -> 55-81 ms (median 75.6 ->
+// 58.6; the longest are those with a deep replica).
 #pragma once
 #include "fs_sched_common.h"
 
@@ -112,13 +112,18 @@ __device__ __forceinline__ int32_t step_of(int64_t ts, int64_t tau, double tau_i
 
 constexpr uint32_t kPTier1 = 0x80000000u;  // a first call, in the key's high word
 constexpr int kAheadBits = 6;              // position among the user's pooled calls
-// Calls the pool takes without looking at whose they are, and a user's share beyond that.
-// 12 slices of the 64 replicas, over 16 seeds: 8.3 to 11.0 ms with 28 and 6, up to 11.2 with
-// 40 and 4, 11.1 with 28 and 3, 11.3 with 48 and 8; 20 and 4 the same, but the whole
-// replicas about 1% slower (57.8 against 56.6 ms).
+// Calls the pool takes without looking at whose they are, and a user's share beyond that.  More
+// room makes more evictions where queues are long, less makes more refills.  In ms, with 28 and
+// 6 / 20 and 4 / 44 and 6 / 28 and 2 / 28 and 12: one replica of 100,000 users 59.2 / 62.4 /
+// 57.7 / 61.5 / 58.2; 64 replicas (three traces) 59.1 / 59.7 / 59.1 / 60.7 / 59.2; 64 with long
+// queues and no interactions 12.1 / 12.3 / 13.3 / 14.5 / 14.3; one of 2,000 users with a long queue
+// 68.9 / 68.4 / 72.9 / 71.8 / 72.2.
 constexpr int kPoolRoom = 28, kPoolShare = 6;
 // A pool of more than kNearMin calls is ranked below the key of rank kNearRank while at least
-// kNearLeast calls are: a ranking costs about 55 clocks a call and a step admits a handful.
+// kNearLeast calls are: a ranking costs about 55 clocks a call and a step admits a handful.  In
+// ms, with 20, 8, 16 / always all / 12, 4, 8 / 32, 8, 28 / 20, 2, 16: 64 replicas (three traces)
+// 59.1 / 62.5 / 60.3 / 60.8 / 59.0, the same in 12 slices 8.70 / 9.33 / 8.80 / 8.93 / 8.66, one
+// replica of 100,000 users 59.2 / 57.5 / 61.3 / 58.4 / 61.1.
 constexpr int kNearMin = 20, kNearLeast = 8, kNearRank = 16;
 
 // A queue that the slot pass serves faster is handed over to it: kDeep spilled calls or more and
@@ -166,9 +171,9 @@ constexpr int kStAdm = 0, kStNone = 1, kStBlk = 2, kStPad = 16;
 // before each, as rank << 26 | tokens (the pool's tokens sum to less than 2^26).  p: the
 // order as one word, all ones in a lane without a ranked call.  The calls are lanes
 // [0, top) of sh, sl (their words) and sa (their tokens | 1 << 26), taken eight at a time
-// by lane reads: new calls take the lowest free lanes, so the pool's own lanes serve.
-// (Reading the words one after the other from LDS, one address for all lanes, took about
-// 95 clocks a call against 55: a 9-call ranking 1,080 clocks against 630.)
+// by lane reads: new calls take the lowest free lanes, so the pool's own lanes serve.  A
+// ranking takes about 300 clocks and 44 to 58 more a call (635 for 8.9 calls on average over 1,024
+// replicas without interactions, 965 for 11.5 over 64 with).
 __device__ __forceinline__ uint32_t pool_rank(uint64_t p, uint32_t sh, uint32_t sl, uint32_t sa, int32_t top) {
   uint32_t acc = 0;
 #pragma unroll
@@ -1117,7 +1122,6 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
           }
           lim = 64;
           nxt = wbase + j1;
-          if (FS_RARE(overflow)) break;
           if (j1 < je || (j1 == 64 && nxt < n)) continue;
         }
       }

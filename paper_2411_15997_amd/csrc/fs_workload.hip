@@ -1,9 +1,10 @@
 // Workload analysis of Sec. 3 on the device: each user's requests and tokens per
 // minute, overall and per application, as histograms of users over exact log2 bins
 // (Fig. 2), the token lengths and interaction sizes per application (Figs. 3-5), and
-// the graph-size table (Table 2).  HBM-bound streaming passes; every accumulation is
-// an integer atomic (order-independent, so results are deterministic), aggregated per
-// wave over the lanes that share a key before it reaches memory.
+// the graph-size table (Table 2).  Streaming passes; every accumulation is an integer
+// atomic (order-independent, so results are deterministic), summed in LDS tables per
+// work-group before it reaches memory, or per wave over the lanes that share a key where
+// the tables do not fit.
 //   1. k_ws_records_hash (k_ws_records for many apps, or more keys than 32 bits)
 //                     per request: validity, the replica's latest arrival, requests and
 //                     tokens per (replica, user, app), the length histograms and sums per

@@ -1,7 +1,7 @@
 """Parity of the scheduler's pool pass (one queued call per lane) with the oracle at the
-edges of its capacities: 64 calls, 64 users, spilled first calls and the reach of their
-links, chains whose next call waits, ties of zero-cost calls, keys too far apart for one
-order word, and the hand-over to the slot pass and back; in one call and in slices."""
+edges of its capacities: 64 calls, 64 users, spilled first calls up to millions of one user,
+chains whose next call waits, ties of zero-cost calls, keys too far apart for one order word,
+and the hand-over to the slot pass and back; in one call and in slices."""
 import numpy as np
 import pytest
 import torch
@@ -39,7 +39,7 @@ def test_pool_edges(users, cap, theta, multi):
 @pytest.mark.parametrize("multi", [False, True])
 @pytest.mark.parametrize("replicas,n", [(1, 20_000), (800, 60), (1, 300)])
 def test_pool_spilled_calls(replicas, n, multi):
-    """A queue longer than the pool (its tail is spilled), and longer than the links reach."""
+    """A queue longer than the pool: its tail is spilled, up to thousands of calls of a user."""
     rng = np.random.default_rng(n + multi)
     say("pool spill", replicas, n, multi)
     tr = tg.concat([random_trace(rng, n, 2, 2, n // 2 + 1, multi=multi, max_tok=8)
