@@ -575,9 +575,9 @@ struct UserSums {
   U128 s1 = {0, 0}, s2 = {0, 0};
   unsigned long long cnt[3] = {0, 0, 0};  // users with a request, fully served, delayed
 };
-__device__ inline UserSums user_sums(const MArgs &a, int32_t r, int64_t k0, int64_t k1) {
+__device__ inline UserSums user_sums(const MArgs &a, int32_t r, uint32_t k0, uint32_t k1) {
   UserSums u;
-  for (int64_t k = k0 + threadIdx.x; k < k1; k += blockDim.x) {  // (k1 may be 2^31 - 1)
+  for (uint32_t k = k0 + threadIdx.x; k < k1; k += blockDim.x) {  // (k1 may be 2^31 - 1)
     const int64_t uk = int64_t(r) * a.t.U + k;
     const uint32_t f = a.uflags[uk];
     const unsigned long long x = a.charged[uk];
@@ -616,8 +616,8 @@ __device__ inline void block_sums(const UserSums &u, SumsLds &sm) {
 __global__ void __launch_bounds__(256) k_m_user_parts(MArgs a) {
   __shared__ SumsLds sm;
   const int32_t r = blockIdx.x / a.parts, p = blockIdx.x % a.parts;
-  const int64_t U = a.t.U, per = (U + a.parts - 1) / a.parts;
-  const int64_t k0 = p * per, k1 = k0 + per < U ? k0 + per : U;
+  const uint32_t U = a.t.U, per = (U + a.parts - 1) / a.parts;  // (k0 + per is below 2^31 + 512)
+  const uint32_t k0 = p * per, k1 = k0 + per < U ? k0 + per : U;
   block_sums(user_sums(a, r, k0, k1), sm);
   if (threadIdx.x == 0) {
     unsigned long long *const o = a.part + int64_t(blockIdx.x) * 8;
@@ -723,8 +723,12 @@ hipError_t launch_metrics(const fs_trace *t, const int64_t *cost, const fs_outpu
   int64_t most_n = 0;
   for (int32_t r = 0; r < t->n_replicas; ++r)
     most_n = std::max<int64_t>(most_n, t->rep_off_h[r + 1] - t->rep_off_h[r]);
-  const int64_t per = std::max<int64_t>(std::max<int64_t>(N / 1024, most_n / 256), kChunkLeast);
-  a.chunk = int32_t(std::min<int64_t>(kChunk, (per + 255) / 256 * 256));
+  // (The wasted-token pass adds one value a chunk: four chunks a CU.)
+  auto chunk_of = [](int64_t per) {
+    return int32_t(std::min<int64_t>(kChunk, (std::max<int64_t>(per, kChunkLeast) + 255) / 256 * 256));
+  };
+  const int32_t wasted_chunk = chunk_of(N / 1024);
+  a.chunk = chunk_of(std::max<int64_t>(N / 1024, most_n / 256));
   if (N > 0) {
     const int64_t chunks = (N + a.chunk - 1) / a.chunk;
     if (t->n_users <= kLdsUsers) {
@@ -737,7 +741,6 @@ hipError_t launch_metrics(const fs_trace *t, const int64_t *cost, const fs_outpu
       const auto interactions = waves ? k_m_interactions_hash<true> : k_m_interactions_hash<false>;
       (void)hipFuncSetAttribute(reinterpret_cast<const void *>(records),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(sizeof(HashLds)));
-      const int32_t chunk = a.chunk;
       // a whole number of work-groups a CU, each of at most kHashChunk records
       const int64_t rounds = (N + int64_t(kHashChunk) * 256 - 1) / (int64_t(kHashChunk) * 256);
       const int64_t per = (N + rounds * 256 - 1) / (rounds * 256);
@@ -746,9 +749,9 @@ hipError_t launch_metrics(const fs_trace *t, const int64_t *cost, const fs_outpu
       hipLaunchKernelGGL(records, dim3(groups), dim3(kHashThreads), sizeof(HashLds), s, a);
       if (t->call)
         hipLaunchKernelGGL(interactions, dim3(groups), dim3(kHashThreads), 0, s, a);
-      a.chunk = chunk;
     }
-    hipLaunchKernelGGL(k_m_wasted, dim3(chunks), dim3(256), 0, s, a);
+    a.chunk = wasted_chunk;
+    hipLaunchKernelGGL(k_m_wasted, dim3((N + wasted_chunk - 1) / wasted_chunk), dim3(256), 0, s, a);
   }
   if (a.parts > 1)
     hipLaunchKernelGGL(k_m_user_parts, dim3(t->n_replicas * a.parts), dim3(256), 0, s, a);
