@@ -127,15 +127,19 @@ constexpr int kPoolRoom = 28, kPoolShare = 6;
 constexpr int kNearMin = 20, kNearLeast = 8, kNearRank = 16;
 
 // A queue that the slot pass serves faster is handed over to it: kDeep spilled calls or more and
-// fewer than kSlowNum / kSlowDen admissions a batch over the last kRateBatches (chains whose next
-// calls have arrived end most batches after one or two calls, and each batch is ranked anew).
-// 64 replicas of 20,000 requests at 0.8 of the capacity take 16.0 ms in the slot pass, 21.1 in
-// the pool and 16.8 with this rule; at 0.6 and never throttled 73.2, 87.0 and 74.7.  64 of
-// 100,000 requests: 16 traces of one kind 75 to 80 ms in the slot pass, up to 88.3 in the pool
-// and 82.4 here, 12 of another 74 to 79, 55 to 89 and 55 to 81.  A rate of 2 (or a look every
-// 128 batches) also hands over queues that the pool serves faster (64.9 -> 74 ms), a rate of 5/3
-// leaves some that it serves slower (82.4 for 78.8); 256 spilled calls instead of 64 16.8 -> 17.1.
-constexpr int kDeep = 64, kSlowNum = 9, kSlowDen = 5, kRateBatches = 512;
+// fewer than kSlow / kSlowDen admissions a batch over the last kRateBatches, or kVeryDeep and
+// fewer than kSlowVery / kSlowDen (chains whose next calls have arrived end most batches after one
+// or two calls, and each batch is ranked anew).  The slot pass takes about 2,300 clocks an
+// admission; the pool 2,150 at 2.1 admissions a batch, 2,300 to 2,430 at 1.8, and from 1,024
+// spilled calls on 2,370 to 2,540 at 2.0 to 2.2 and up to 2,790 at 1.8.  In ms, slot pass alone /
+// pool alone / this rule: 64 replicas of 20,000 requests at 0.8 of the capacity 16.0 / 21.1 /
+// 16.9, at 0.6 and never throttled 73.2 / 86.6 / 74.4; 64 of 100,000 without limits 92.2 / 121.7 /
+// 97.4 and with equal weights 96.7 / 121.6 / 100.5; with limits, 12 traces, 75-80 / 77-88 / 75-83
+// and 16 of another kind 74-79 / 52-90 / 52-82.  A rate of 2 from 64 calls on (or a look every 128
+// batches) also hands over queues that the pool serves faster (65 -> 74), as does kVeryDeep at
+// 1,024 (65 -> 68); a rate of 5/3 leaves some that it serves slower (82.4 for 78.8), as does
+// kDeep at 256 (16.8 -> 17.1).
+constexpr int kDeep = 64, kVeryDeep = 1536, kSlow = 9, kSlowVery = 11, kSlowDen = 5, kRateBatches = 512;
 constexpr int32_t kOutDeep = 3;  // rs->overflow of a replica handed over for its queue
 
 // A slot's record: the counter after the user's pooled calls; the number of pooled calls, of
@@ -1073,8 +1077,8 @@ __device__ __forceinline__ void pool_replica(const SchedArgs &a, char *smem, boo
         const int32_t batches = cuts + (s - s_look);
         if (LINKS && batches >= kRateBatches) {
           // (the slot pass rebuilds the queue first: not for fewer steps than queued calls)
-          deep = sp_total >= kDeep && int64_t(seq - seq_look) * kSlowDen < int64_t(batches) * kSlowNum &&
-                 s_end - s >= int64_t(sp_total);
+          deep = sp_total >= kDeep && s_end - s >= int64_t(sp_total) &&
+                 int64_t(seq - seq_look) * kSlowDen < int64_t(batches) * (sp_total < kVeryDeep ? kSlow : kSlowVery);
           if (deep) {
             overflow = true;
             break;
