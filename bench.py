@@ -44,9 +44,9 @@ STAGE_SRC = {
 # (bench.py --calib-copy).  Keyed by workload and stage; an entry counts only while
 # the stage's sources hash to `src`.
 MEASURED_TRAFFIC = {
-    # k_schedule_onchip on the 1,024-replica weight sweep (20.48M requests)
-    ("c4_sweep", "schedule"): {"src": "df9073c9ab2d1903", "fetch_kib": 313379.0,
-                               "write_kib": 137709.46875, "fetch_factor": 1.99991,
+    # k_schedule_pool on the 1,024-replica weight sweep (20.48M requests)
+    ("c4_sweep", "schedule"): {"src": "447e3dc9ebe9b8b4", "fetch_kib": 305169.125,
+                               "write_kib": 137354.375, "fetch_factor": 1.99991,
                                "write_factor": 1.0},
     # every kernel of one fs_throttle call on the 50M-request throttle stream
     ("c3_throttle", "throttle"): {"src": "f12662f2bb0b6f6c", "fetch_kib": 1287878.3125,
